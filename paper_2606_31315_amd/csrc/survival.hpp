@@ -10,8 +10,9 @@
 //   survival_tau_kernel     one thread per sample: tau for every candidate, B*, the regret of
 //                           B_hat and L_tau.  A workgroup stages its samples' gamma rows
 //                           through LDS so the HBM reads are contiguous 16-byte vectors.
-//   survival_sample_kernel  Monte Carlo of L_b(x): one wavefront per (sample, candidate), one
-//                           lane per trial in turn.  Uniforms come from Philox4x64-10 (Salmon
+//   survival_sample_kernel  Monte Carlo of L_b(x): a wavefront (or a workgroup, where pairs are few)
+//                           per (sample, candidate), one trial per lane, the next one as soon as
+//                           it ends.  Uniforms come from Philox4x64-10 (Salmon
 //                           et al., SC'11) keyed by (seed, 0) at counter ((i-1)/4, t, c, n), word
 //                           (i-1) mod 4 for drafted position i, as the top 53 bits over 2^53, so
 //                           every trial's draws are fixed by its indices alone.
@@ -123,83 +124,169 @@ __global__ __launch_bounds__(256) void survival_tau_kernel(SurvivalArgs a) {
 }
 
 // ---- Philox4x64-10 ----
-struct Philox4x64 {
-  unsigned long long v[4];
+constexpr unsigned long long kPhiloxM0 = 0xD2E7470EE14C6C93ull, kPhiloxM1 = 0xCA5A826395121157ull;
+constexpr unsigned long long kPhiloxW0 = 0x9E3779B97F4A7C15ull, kPhiloxW1 = 0xBB67AE8584CAA73Bull;
+
+struct U128 {
+  unsigned long long hi, lo;
 };
 
-__device__ __forceinline__ Philox4x64 philox4x64_10(unsigned long long c0, unsigned long long c1,
-                                                    unsigned long long c2, unsigned long long c3,
-                                                    unsigned long long k0, unsigned long long k1) {
-  constexpr unsigned long long M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
-  constexpr unsigned long long W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const unsigned long long hi0 = __umul64hi(M0, c0), lo0 = M0 * c0;
-    const unsigned long long hi1 = __umul64hi(M1, c2), lo1 = M1 * c2;
-    const unsigned long long n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0;
-    c1 = lo1;
-    c2 = n2;
-    c3 = lo0;
-    k0 += W0;
-    k1 += W1;
-  }
-  return Philox4x64{{c0, c1, c2, c3}};
+// m * x, 64 x 64 -> 128 bits, in seven instructions: every instruction of gfx950 used here costs
+// about the same issue slot, v_mad_u64_u32 (32 x 32 + 64 -> 64) included, so what counts is how
+// many there are.  The middle products are summed into 65 bits, the carry left by the multiply-add
+// in a scalar pair, rather than split into 32-bit halves that the next product would need
+// zero-extended (seven moves and additions per product more).
+__device__ __forceinline__ U128 mul_join(unsigned long long p0, unsigned long long mid, unsigned long long carry,
+                                         unsigned mh, unsigned xh) {
+  unsigned c;
+  // s_nop: the scalar pair was just written by a VALU instruction
+  asm("s_nop 1\n\tv_cndmask_b32 %0, 0, 1, %1" : "=v"(c) : "s"(carry));
+  const unsigned long long m2 = ((unsigned long long)c << 32) | (mid >> 32);
+  return U128{(unsigned long long)mh * xh + m2, (mid << 32) | (unsigned)p0};
+}
+__device__ __forceinline__ unsigned long long high_word(unsigned long long v) {
+  unsigned long long r;
+  asm("v_lshrrev_b64 %0, 32, %1" : "=v"(r) : "v"(v));
+  return r;
+}
+__device__ __forceinline__ U128 mul_full(unsigned long long m, unsigned long long x) {
+  const unsigned ml = (unsigned)m, mh = (unsigned)(m >> 32), xl = (unsigned)x, xh = (unsigned)(x >> 32);
+  const unsigned long long p0 = (unsigned long long)ml * xl;
+  const unsigned long long p1 = (unsigned long long)mh * xl + high_word(p0);  // no carry out
+  unsigned long long mid, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(mid), "=s"(carry) : "s"(ml), "v"(xh), "v"(p1));
+  return mul_join(p0, mid, carry, mh, xh);
 }
 
-__device__ __forceinline__ double u53(unsigned long long w) {
-  return (double)(w >> 11) * (1.0 / 9007199254740992.0);
+__device__ __forceinline__ unsigned long long xor3(unsigned long long a, unsigned long long b, unsigned long long c) {
+  const unsigned lo = __builtin_amdgcn_bitop3_b32((unsigned)a, (unsigned)b, (unsigned)c, 0x96);
+  const unsigned hi = __builtin_amdgcn_bitop3_b32((unsigned)(a >> 32), (unsigned)(b >> 32), (unsigned)(c >> 32), 0x96);
+  return ((unsigned long long)hi << 32) | lo;
 }
+
+// q as the threshold of a draw: with u the top 53 bits of word w over 2^53, u < q iff
+// w <= draw_limit(q), for every q > 0 (u < q iff w >> 11 < ceil(q 2^53); scaling by 2^53 is exact).
+__device__ __forceinline__ unsigned long long draw_limit(double q) {
+  return q >= 1.0 ? ~0ull : ((unsigned long long)ceil(q * 9007199254740992.0) << 11) - 1ull;
+}
+
+// What one Philox block of four draws needs besides the trial index, per block of a (sample,
+// candidate) pair.  The counter is (blk, t, c, n): the first round's products and the second
+// round's second one do not depend on the trial.
+struct alignas(16) DrawBlock {
+  unsigned long long limit[4];  // draw_limit(q) of the block's positions
+  unsigned long long c0, c1;    // words 0 and 1 after two rounds
+  unsigned long long x2;        // word 2 after two rounds, xor-ed with the high half of M0 * word 0
+  unsigned long long pad;
+};
 
 constexpr int kSurvWavesPerWg = 4;
 
-// Dynamic LDS per wavefront: q_1..q_b (doubles), then the histogram of L (P + 1 ints).
+// Bytes of dynamic LDS per pair: its DrawBlocks, then the histogram of L (P + 1 ints).
+__host__ __device__ inline int surv_pair_lds(int P) { return ((P + 3) / 4) * (int)sizeof(DrawBlock) + ((P + 4) / 4) * 16; }
+
+// WPP wavefronts per (sample, candidate) pair, kSurvWavesPerWg / WPP pairs per workgroup.
+// Bound by the instructions of the draws' 64-bit products (about 180 per block of four draws).
+// Trials end after one to b / 4 blocks of draws (1.8 on average where gamma ~ U(0.6, 0.97)), so a
+// lane that is done takes the pair's next trial at once instead of waiting for the wavefront's
+// longest one; the products no trial changes are tabled per block; and a draw is compared as an
+// integer.  65536 samples x 5 candidates x 1024 trials: one lane per trial in turn, two full rounds
+// more and fp64 compares 8617 us; with these 3462 us; with the products in seven instructions
+// (mul_full) and three-input xors 3046 us.
+template <int WPP>
 __global__ __launch_bounds__(256) void survival_sample_kernel(SurvivalArgs a) {
-  extern __shared__ __attribute__((aligned(16))) double slds[];
+  extern __shared__ __attribute__((aligned(16))) char slds[];
+  __shared__ unsigned long long sh_sum[kSurvWavesPerWg];
+  constexpr int NT = 64 * WPP;  // threads per pair
   const int P = a.P, C = a.C;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int per_wave = P + (P + 2) / 2;  // P doubles of q, then P + 1 ints (rounded up to doubles)
-  double *q = slds + wave * per_wave;
-  int *hist = reinterpret_cast<int *>(q + P);
-  const long long pair = (long long)blockIdx.x * kSurvWavesPerWg + wave;
-  if (pair >= (long long)a.N * C) return;  // wave-uniform; no workgroup barrier follows
-  const long long n = pair / C;
-  const int c = (int)(pair % C);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wp = wave % WPP, tp = wp * 64 + lane;
+  DrawBlock *tab = reinterpret_cast<DrawBlock *>(slds + (wave / WPP) * surv_pair_lds(P));
+  int *hist = reinterpret_cast<int *>(tab + (P + 3) / 4);
+  const long long pair = (long long)blockIdx.x * (kSurvWavesPerWg / WPP) + wave / WPP;
+  const bool live = pair < (long long)a.N * C;
+  const long long n = live ? pair / C : 0;
+  const int c = live ? (int)(pair % C) : 0;
   const int b = a.cands[c];
   const double r = retention(b, a.train_block, a.alpha);
-  for (int i = lane; i < b; i += 64) q[i] = (double)a.gamma[n * P + i] * r;
-  for (int i = lane; i <= P; i += 64) hist[i] = 0;
-  // the wavefront's own LDS writes, visible to all of its lanes
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  unsigned long long sum = 0;
-  for (int t = lane; t < a.trials; t += 64) {
-    int L = 0;
-    bool alive = true;
-    for (int blk = 0; alive && 4 * blk < b; ++blk) {
-      const Philox4x64 w = philox4x64_10((unsigned long long)blk, (unsigned long long)t, (unsigned long long)c,
-                                         (unsigned long long)n, a.seed, 0ull);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int i = 4 * blk + k;
-        if (!alive || i >= b) break;
-        if (u53(w.v[k]) < q[i]) ++L;
-        else alive = false;
-      }
-    }
-    sum += (unsigned long long)L;
-    if (a.len_hist) atomicAdd(&hist[L], 1);
+  // key schedule of the first two rounds; the counter words of round 1 that no trial changes
+  const unsigned long long k0 = a.seed, k0b = a.seed + kPhiloxW0, k1b = kPhiloxW1;
+  const U128 m1 = mul_full(kPhiloxM1, (unsigned long long)c);
+  // Positions from the first q <= 0 (or NaN) on accept nothing: they end the block early.
+  int be = b;
+  for (int i0 = 0; i0 < b && live; i0 += 64) {
+    const int i = i0 + lane;
+    const double q = i < b ? (double)a.gamma[n * P + i] * r : 1.0;
+    const unsigned long long dead = __ballot(!(q > 0.0));
+    if (dead) be = min(be, i0 + __ffsll((long long)dead) - 1);
+    if (wp == 0 && i < b) tab[i >> 2].limit[i & 3] = draw_limit(q > 0.0 ? q : 1.0);
   }
-  // wavefront sum of the lengths (exact integers)
+  const int nblk = (be + 3) / 4;
+  for (int k = tp; k < nblk && live; k += NT) {
+    const U128 m0 = mul_full(kPhiloxM0, (unsigned long long)k);
+    const U128 m1b = mul_full(kPhiloxM1, m0.hi ^ (unsigned long long)n);  // k1 = 0 in round 1
+    tab[k].c0 = m1b.hi ^ m1.lo ^ k0b;
+    tab[k].c1 = m1b.lo;
+    tab[k].x2 = m0.lo ^ k1b;
+  }
+  for (int i = tp; i <= P; i += NT) hist[i] = 0;
+  __syncthreads();
+  unsigned long long sum = 0;
+  if (live) {
+    const unsigned long long w0 = m1.hi ^ k0;  // word 0 after round 1 is w0 ^ t
+    const int t_end = (int)((long long)a.trials * (wp + 1) / WPP);
+    int next = (int)((long long)a.trials * wp / WPP);  // wavefront-uniform: the next trial to hand out
+    int t = next + lane, blk = 0;
+    next += 64;
+    bool act = t < t_end && be > 0;
+    while (__any(act)) {
+      const DrawBlock d = tab[blk];
+      const U128 p = mul_full(kPhiloxM0, w0 ^ (unsigned long long)(unsigned)t);
+      unsigned long long c0 = d.c0, c1 = d.c1, c2 = p.hi ^ d.x2, c3 = p.lo;
+      unsigned long long ka = k0b, kb = k1b;
+#pragma unroll
+      for (int rd = 2; rd < 10; ++rd) {
+        ka += kPhiloxW0;
+        kb += kPhiloxW1;
+        const U128 x = mul_full(kPhiloxM0, c0), y = mul_full(kPhiloxM1, c2);
+        c0 = xor3(y.hi, c1, ka);
+        c1 = y.lo;
+        c2 = xor3(x.hi, c3, kb);
+        c3 = x.lo;
+      }
+      const unsigned acc = (c0 <= d.limit[0] ? 1u : 0u) | (c1 <= d.limit[1] ? 2u : 0u) | (c2 <= d.limit[2] ? 4u : 0u) |
+                           (c3 <= d.limit[3] ? 8u : 0u);
+      const int lead = __ffs((int)~acc) - 1;  // leading acceptances of the block, 0..4
+      const bool end = act && (lead < 4 || 4 * blk + 4 >= be);
+      const unsigned long long em = __ballot(end);
+      if (end) {
+        const int L = min(4 * blk + lead, be);
+        sum += (unsigned)L;
+        if (a.len_hist) atomicAdd(&hist[L], 1);
+        t = next + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(em >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)em, 0u));
+        blk = 0;
+        act = t < t_end;
+      } else {
+        blk = act ? blk + 1 : 0;
+      }
+      next += __popcll(em);
+    }
+    if (be == 0 && tp == 0 && a.len_hist) hist[0] = a.trials;
+  }
+  // sum of the lengths (exact integers)
   for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  if (lane == 0) a.mean_len[pair] = (double)sum / (double)a.trials;
+  if (WPP > 1 && lane == 0) sh_sum[wave] = sum;
+  __syncthreads();
+  if (!live) return;
+  if constexpr (WPP > 1) {
+    sum = 0;
+#pragma unroll
+    for (int w = 0; w < WPP; ++w) sum += sh_sum[(wave / WPP) * WPP + w];
+  }
+  if (tp == 0) a.mean_len[pair] = (double)sum / (double)a.trials;
   if (a.len_hist) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     int *out = a.len_hist + pair * (P + 1);
-    for (int i = lane; i <= P; i += 64) out[i] = hist[i];
+    for (int i = tp; i <= P; i += NT) out[i] = hist[i];
   }
 }
 

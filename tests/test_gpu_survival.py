@@ -128,3 +128,23 @@ def test_sample_full_size_sampled_pairs():
     rng = np.random.default_rng(1)
     pairs = [(0, 0), (p.N - 1, 4)] + [(int(n), int(c)) for n, c in zip(rng.choice(p.N, 22), rng.integers(0, 5, 22))]
     _sample_check(p, seed=2024, trials=1024, pairs=pairs)
+
+
+@pytest.mark.parametrize("N,trials", [(1, 1), (2, 63), (2, 65), (3, 255), (3, 257), (682, 256), (683, 256)])
+def test_sample_trial_refill_edges(N, trials):
+    """Trial counts about a wavefront and about the sharing threshold, and pair counts on both sides
+    of it (3 candidates: 2046 and 2049 pairs); positions that always or never accept, in the
+    middle of a block of four draws, at its ends and past the candidate.  Counts are exact."""
+    p = W.make_survival(45, N=N, P=19, train_block=9, radius=1, alpha=0.002)
+    p.gamma[0, 0:8] = 1.0
+    p.gamma[0, 6] = 0.0
+    if N > 1:
+        p.gamma[1, :] = 1.5
+        p.gamma[1, 8] = np.nan
+        p.gamma[-1, :4] = [1.0, 1.0, 1.0, 1e-300]
+    pairs = None if N < 10 else [(0, 0), (0, 2), (1, 1), (1, 2), (N - 1, 0), (N - 1, 2), (N // 2, 1)]
+    mean, hist = _sample_check(p, seed=99 + trials, trials=trials, pairs=pairs)
+    assert (hist[0, :, 7:] == 0).all()
+    nohist, none = sd.survival_sample(torch.from_numpy(p.gamma).to(G.dev()), p.cands, p.train_block, p.alpha,
+                                      99 + trials, trials, hist=False)
+    assert none is None and np.array_equal(nohist.cpu().numpy(), mean)
