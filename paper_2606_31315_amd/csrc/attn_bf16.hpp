@@ -29,17 +29,7 @@
 
 namespace sdb {
 
-#define SDB_LDS __attribute__((address_space(3)))
-
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-// Two fp32 -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32).
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-  const f32x2v v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
-}
 
 // ds_read_b64_tr_b16 issued as inline assembly: the intrinsic form makes the compiler
 // assume it may alias the in-flight load-to-LDS writes and wait for all of them (the
@@ -257,19 +247,6 @@ __device__ __forceinline__ void pv_mma(const f32x4 (&p)[NSB], s16x4 (&vv)[NDT][2
                       vv[dt][1][0], vv[dt][1][1], vv[dt][1][2], vv[dt][1][3]};
     oacc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v8), pb, oacc[dt], 0, 0, 0);
   }
-}
-
-// The value of lane l combined with lane l ^ 16 (x16) or l ^ 32 (x32), by the gfx950 lane-swap
-// instructions: v_permlane16_swap / v_permlane32_swap with both operands x return, in every lane,
-// its own value and its partner's (one in each result), in VALU cycles instead of the LDS round
-// trip of a ds_bpermute shuffle.
-__device__ __forceinline__ float2 pair_x16(float x) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return float2{__uint_as_float(p[0]), __uint_as_float(p[1])};
-}
-__device__ __forceinline__ float2 pair_x32(float x) {
-  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return float2{__uint_as_float(p[0]), __uint_as_float(p[1])};
 }
 
 // APPEND: the block's keys and values are read from a.k_new / a.v_new rather than the cache,

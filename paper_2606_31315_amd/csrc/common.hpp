@@ -5,6 +5,8 @@
 #include <limits.h>
 #include <stdint.h>
 
+#define SDB_LDS __attribute__((address_space(3)))
+
 namespace sdb {
 
 constexpr int kWave = 64;     // CDNA wavefront width
@@ -35,6 +37,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
+}
+
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+
+// Two fp32 -> packed bf16 pair, round to nearest even (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
+  const f32x2v v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -169,6 +180,19 @@ __device__ __forceinline__ int wave_max_i(int x) {
   x = max(x, __builtin_amdgcn_update_dpp(INT_MIN, x, 0x121, 0xf, 0xf, false));
   return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
              max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+
+// The value of lane l combined with lane l ^ 16 (x16) or l ^ 32 (x32), by the gfx950 lane-swap
+// instructions: v_permlane16_swap / v_permlane32_swap with both operands x return, in every lane,
+// its own value and its partner's (one in each result), in VALU cycles instead of the LDS round
+// trip of a ds_bpermute shuffle.
+__device__ __forceinline__ float2 pair_x16(float x) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return float2{__uint_as_float(p[0]), __uint_as_float(p[1])};
+}
+__device__ __forceinline__ float2 pair_x32(float x) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return float2{__uint_as_float(p[0]), __uint_as_float(p[1])};
 }
 
 // Workgroup id remapped so that consecutive logical ids land on the same XCD:

@@ -323,6 +323,11 @@ int check_cache_shape(const sd_attn_shape *sh, const char *what) {
 
 struct PolicyPlan {
   size_t off_stats, off_h1, off_h2, total;
+  // the layers on matrix cores (matrix: this shape takes them): vocabulary chunks and the workspace
+  // with their partials, the larger of the two layouts
+  int matrix;
+  int nch;
+  size_t off_part, off_h1m, off_h2m, total_m;
 };
 
 int policy_plan(const sd_policy_shape *sh, PolicyPlan *p) {
@@ -348,6 +353,24 @@ int policy_plan(const sd_policy_shape *sh, PolicyPlan *p) {
   p->off_h2 = off;
   off = align256(off + P * sh->hidden * sizeof(float));
   p->total = off > 0 ? off : 256;
+  // From three prompts on, or where W1's rows are whole 128-byte lines, the matrix cores' first layer
+  // is the faster one (us per call, dense / matrix, H = 2048: V = 151936 P = 1 122.0 / 106.3, P = 8
+  // 294 / 108.6, V = 32000 P = 1 38.2 / 36.1; rows off the lines: V = 100008 P = 1 86.3 / 97.2, V = 50000
+  // P = 2 55.3 / 57.5; H = 1000, V = 30000: P = 1 20.5 / 27.5, P = 3 30.9 / 28.7).
+  p->matrix = P > 2 || sh->vocab % sdb::kFirstKT == 0;
+  // chunks: one workgroup per CU (its ring fills the LDS), two tiles or more each
+  const int groups = (sh->hidden + sdb::kFirstRows - 1) / sdb::kFirstRows;
+  const int tiles = (sh->vocab + sdb::kFirstKT - 1) / sdb::kFirstKT;
+  p->nch = std::max(1, std::min(std::max(8, 256 / groups), tiles / 2));
+  const size_t pass = std::min(P, (size_t)sdb::kFirstPrompts);
+  off = align256(p->nch * pass * sizeof(float2));
+  p->off_part = off;
+  off = align256(off + p->nch * pass * sh->hidden * sizeof(float));
+  p->off_h1m = off;
+  off = align256(off + pass * sh->hidden * sizeof(float));
+  p->off_h2m = off;
+  off = align256(off + P * sh->hidden * sizeof(float));
+  p->total_m = p->matrix ? off : 0;
   return ok();
 }
 
@@ -1028,7 +1051,7 @@ int sd_policy_workspace_size(const sd_policy_shape *shape, size_t *bytes) {
   PolicyPlan p;
   int rc = policy_plan(shape, &p);
   if (rc) return rc;
-  *bytes = p.total;
+  *bytes = std::max(p.total, p.total_m);
   return ok();
 }
 
@@ -1055,24 +1078,47 @@ int sd_block_size_policy(const sd_policy_shape *sh, const void *last_logits, con
   pa.P = P;
   pa.V = V;
   pa.logits_bf16 = sh->logits_dtype == SD_BF16;
-  const dim3 gsoft(P * sdb::kPolicyChunks);
-  if (pa.logits_bf16) hipLaunchKernelGGL(sdb::policy_stats_kernel<true>, gsoft, dim3(256), 0, st, pa);
-  else hipLaunchKernelGGL(sdb::policy_stats_kernel<false>, gsoft, dim3(256), 0, st, pa);
-  float *h1 = (float *)(ws + p.off_h1), *h2 = (float *)(ws + p.off_h2);
-  // dense layers in groups of kPolicyMaxPrompts prompts (each group reads the weights once);
-  // the first takes the logits and makes p = softmax(z) from the chunk records on the fly
   const size_t zb = pa.logits_bf16 ? 2 : 4;
-  for (int g0 = 0; g0 < P; g0 += sdb::kPolicyMaxPrompts) {
-    const int np = std::min(sdb::kPolicyMaxPrompts, P - g0);
-    sdb::DenseArgs d1{(const uint16_t *)w1, (const char *)last_logits + (size_t)g0 * V * zb, b1,
-                      h1 + (size_t)g0 * H, H, V, np, pa.stats + (size_t)g0 * sdb::kPolicyChunks};
-    if (pa.logits_bf16) launch_dense<true, 1>(d1, st);
-    else launch_dense<true, 2>(d1, st);
-    sdb::DenseArgs d2{(const uint16_t *)w2, h1 + (size_t)g0 * H, b2, h2 + (size_t)g0 * H, H, H, np, nullptr};
-    launch_dense<true, 0>(d2, st);
+  float *h1 = (float *)(ws + p.off_h1), *h2 = (float *)(ws + p.off_h2);
+  // a workspace of the dense layout alone gets the dense kernels
+  if (p.matrix && workspace_bytes >= p.total_m) {
+    float *h1m = (float *)(ws + p.off_h1m);
+    h2 = (float *)(ws + p.off_h2m);
+    for (int g0 = 0; g0 < P; g0 += sdb::kFirstPrompts) {
+      const int np = std::min(sdb::kFirstPrompts, P - g0);
+      sdb::FirstArgs f{(const uint16_t *)w1, (const char *)last_logits + (size_t)g0 * V * zb,
+                       (float *)(ws + p.off_part), (float2 *)ws, H, V, np, p.nch};
+      const dim3 gf(p.nch * ((H + sdb::kFirstRows - 1) / sdb::kFirstRows)), tf(64 * sdb::kFirstWaves);
+      sdb::MergeArgs mg{f.part, f.stats, b1, h1m, f.w, f.logits, H, V, np, p.nch};
+      const dim3 gm(np * ((H + 63) / 64));
+      if (pa.logits_bf16) {
+        hipLaunchKernelGGL(sdb::policy_first_kernel<true>, gf, tf, 0, st, f);
+        hipLaunchKernelGGL(sdb::policy_merge_kernel<true>, gm, dim3(256), 0, st, mg);
+      } else {
+        hipLaunchKernelGGL(sdb::policy_first_kernel<false>, gf, tf, 0, st, f);
+        hipLaunchKernelGGL(sdb::policy_merge_kernel<false>, gm, dim3(256), 0, st, mg);
+      }
+      sdb::SecondArgs d{(const uint16_t *)w2, mg.y, b2, h2 + (size_t)g0 * H, H, np};
+      hipLaunchKernelGGL(sdb::policy_second_kernel, dim3((H + 15) / 16), dim3(64 * sdb::kSecondWaves), 0, st, d);
+    }
+  } else {
+    const dim3 gsoft(P * sdb::kPolicyChunks);
+    if (pa.logits_bf16) hipLaunchKernelGGL(sdb::policy_stats_kernel<true>, gsoft, dim3(256), 0, st, pa);
+    else hipLaunchKernelGGL(sdb::policy_stats_kernel<false>, gsoft, dim3(256), 0, st, pa);
+    // dense layers in groups of kPolicyMaxPrompts prompts (each group reads the weights once);
+    // the first takes the logits and makes p = softmax(z) from the chunk records on the fly
+    for (int g0 = 0; g0 < P; g0 += sdb::kPolicyMaxPrompts) {
+      const int np = std::min(sdb::kPolicyMaxPrompts, P - g0);
+      sdb::DenseArgs d1{(const uint16_t *)w1, (const char *)last_logits + (size_t)g0 * V * zb, b1,
+                        h1 + (size_t)g0 * H, H, V, np, pa.stats + (size_t)g0 * sdb::kPolicyChunks};
+      if (pa.logits_bf16) launch_dense<true, 1>(d1, st);
+      else launch_dense<true, 2>(d1, st);
+      sdb::DenseArgs d2{(const uint16_t *)w2, h1 + (size_t)g0 * H, b2, h2 + (size_t)g0 * H, H, H, np, nullptr};
+      launch_dense<true, 0>(d2, st);
+    }
   }
   sdb::HeadArgs ha{(const uint16_t *)w3, h2, b3, scores, block_size, C, H, sh->base_block, sh->radius};
-  hipLaunchKernelGGL(sdb::policy_head_kernel, dim3(P), dim3(256), 0, st, ha);
+  hipLaunchKernelGGL(sdb::policy_head_kernel, dim3(P), dim3(64 * std::min(16, C)), 0, st, ha);
   return check_launch("sd_block_size_policy");
 }
 

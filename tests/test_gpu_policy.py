@@ -51,3 +51,59 @@ def test_qwen3_vocab_hidden_2048(P):
     """The paper's predictor: V = 151936 (Qwen3), two hidden layers of 2048, k = 2 around B = 16;
     11 prompts exercise two groups of the dense passes."""
     _check(W.make_policy(63 + P, P=P, V=151936, H=2048, radius=2, dtype="bf16"))
+
+
+def _dense_bytes(P, H):
+    """Workspace of the dense kernels alone: chunk records, then two layers of activations."""
+    up = lambda n: (n + 255) // 256 * 256
+    return up(P * 64 * 8) + 2 * up(P * H * 4)
+
+
+def _call(pp, ws=None):
+    dev = G.dev()
+    f = lambda x: torch.from_numpy(x).to(dev)
+    sc, bs = sd.block_size_policy(pp.logits.to(dev), pp.w1.to(dev), f(pp.b1), pp.w2.to(dev), f(pp.b2), pp.w3.to(dev),
+                                  f(pp.b3), pp.base_block,
+                                  workspace=None if ws is None else torch.empty(ws, dtype=torch.uint8, device=dev))
+    torch.cuda.synchronize()
+    return sc.cpu().numpy(), bs.cpu().numpy()
+
+
+@pytest.mark.parametrize("P,V,H,dtype", [(1, 64, 8, "bf16"), (3, 8, 8, "f32"), (3, 72, 24, "bf16"), (16, 632, 520, "f32"),
+                                         (17, 1288, 72, "bf16"), (4, 2040, 1032, "bf16"), (1, 4160, 512, "f32"),
+                                         (2, 1000, 64, "bf16")])
+def test_matrix_layers_edges(P, V, H, dtype):
+    """Vocabularies below, at and past a 64-element tile, partial rows of the 64- and 512-row groups
+    and of the 16-row tiles, one more prompt than a pass holds; and the dense kernels, which a
+    workspace of their size alone still gets, on the same inputs."""
+    pp = W.make_policy(80 + P, P=P, V=V, H=H, radius=2, dtype=dtype)
+    sc, _ = _check(pp)
+    dense, _ = _call(pp, _dense_bytes(P, H))
+    # both within the fp64 oracle's band of 1e-4 + 1e-4 |o|, so within twice that of each other
+    assert (np.abs(sc - dense) <= 2e-4 + 2e-4 * np.abs(dense)).all()
+
+
+def test_matrix_layers_special_values():
+    """Prompts with -inf logits (a whole chunk of them too), only -inf, +inf and NaN; weights that are
+    infinite, NaN, or infinite where p underflows to 0: the dense kernels' values, NaN for NaN."""
+    P, V, H = 6, 4096, 64
+    pp = W.make_policy(97, P=P, V=V, H=H, radius=2, dtype="bf16")
+    pp.logits[1, :1500] = float("-inf")
+    pp.logits[2, :] = float("-inf")
+    pp.logits[3, 77] = float("inf")
+    pp.logits[4, 4000] = float("nan")
+    dense, _ = _call(pp, _dense_bytes(P, H))
+    sc, bs = _call(pp)
+    assert np.allclose(sc, dense, rtol=2e-4, atol=2e-4, equal_nan=True)
+    ok = _check(W.PolicyProblem(pp.logits[:2], *[getattr(pp, k) for k in ("w1", "b1", "w2", "b2", "w3", "b3", "base_block",
+                                                                          "radius", "dtype")]))
+    assert np.isfinite(ok[0]).all()
+    pp.w1[5, 100] = float("inf")
+    pp.w1[6, 4095] = float("-inf")
+    pp.w1[7, 9] = float("nan")
+    pp.logits[5, 100] = -1e4  # p = 0 there: 0 times infinity
+    dense, _ = _call(pp, _dense_bytes(P, H))
+    sc, _ = _call(pp)
+    assert np.array_equal(np.isnan(sc), np.isnan(dense)) and np.array_equal(np.isinf(sc), np.isinf(dense))
+    fin = np.isfinite(dense)
+    assert np.allclose(sc[fin], dense[fin], rtol=2e-4, atol=2e-4)
