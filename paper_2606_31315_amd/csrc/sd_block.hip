@@ -17,6 +17,7 @@
 #include "accept.hpp"
 #include "attn.hpp"
 #include "attn_bf16.hpp"
+#include "attn_f32.hpp"
 #include "check.hpp"
 #include "kvstep.hpp"
 #include "policy.hpp"
@@ -67,7 +68,12 @@ constexpr int kBf16KT = SDB_BF16_KT, kBf16NS = SDB_BF16_NS;
 // ---------------------------------------------------------------------------
 struct AttnPlan {
   int G, KT, split_len, max_splits, Mpad, n_work, per_xcd, grid, dense, MT;
-  int bal;  // balanced shares (bf16; see bal_share)
+  int bal;  // balanced shares (see bal_share)
+  int bal_grid;
+  // fp32: m-tiles per group at most, groups of the largest block, rows of a partial slot, and the
+  // workspace of the plan before this one (even splits): a caller's of that size is still taken
+  int group_mt, groups, part_rows;
+  size_t min_total;
   int ve;   // bf16 with one m-tile per wavefront and blocks of 7-8 m-tiles: early V^T reads (VE)
   size_t off_ml, off_o, total;
 };
@@ -76,6 +82,16 @@ struct AttnPlan {
 // share at least 16 key tiles (1024 keys), like the shortest split of the other multi-wave plans.
 constexpr int kBalGrid = 256;
 constexpr int kBalMinTiles = 16;
+#ifndef SDB_F32_MIN_TILES
+#define SDB_F32_MIN_TILES 2
+#endif
+constexpr int kBalMinTilesF32 = SDB_F32_MIN_TILES;  // shortest fp32 share, in 64-key tiles
+
+// Workspace of an fp32 balanced plan of `grid` workgroups.
+size_t f32_bytes(const AttnPlan &p, long long pairs, int D, long long grid) {
+  const size_t rows = (size_t)(grid + pairs * p.groups) * p.part_rows;
+  return align256(rows * sizeof(float2)) + align256(rows * D * sizeof(float)) + 256;  // and the plan's word
+}
 
 int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   if (!sh) return fail(SD_ERR_INVALID_ARG, "sd_block_attn: shape is NULL");
@@ -99,7 +115,8 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   if (!(sh->scale >= 0.f) || isinf(sh->scale)) return fail(SD_ERR_INVALID_ARG, "scale must be finite and >= 0");
 
   p->G = G;
-  p->KT = (sh->dtype == SD_BF16) ? kBf16KT : 32;
+  const bool f32 = sh->dtype == SD_F32;
+  p->KT = f32 ? 32 : kBf16KT;
   const long long max_L = (long long)sh->max_ctx + sh->max_block;
   const long long pairs = (long long)S * Hkv;
   // Split the keys so that, at the maximum length, the grid is one wave: one workgroup per
@@ -151,7 +168,8 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   // of all the pairs' (weighted) key tiles instead (bal_share), in the plain, paged and
   // fused-append calls alike.  Partial slots: one per workgroup and pair a share touches, at
   // most kBalGrid + pairs.
-  p->bal = sh->dtype == SD_BF16 && p->dense && p->max_splits > 1;
+  p->bal = !f32 && p->dense && p->max_splits > 1;
+  p->bal_grid = kBalGrid;
   {  // the device sums tile weights (at most kBalWeightMax8 + 4 per m-tile past 8) in 32-bit integers
     const long long nmt_max = (G * (long long)sh->max_block + 15) / 16;
     const long long wmax = sdb::kBalWeightMax8 + 4 * std::max(0LL, nmt_max - 8);
@@ -159,21 +177,42 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   }
   const long long slots = p->bal ? std::max(nw, (long long)kBalGrid + pairs) : nw;
   const int nmt = p->Mpad / 16;
-  if (sh->dtype == SD_BF16) p->MT = nmt <= 8 ? 1 : 2;  // 8 wavefronts, 1 or 2 m-tiles each
-  else p->MT = nmt <= 4 ? 1 : nmt <= 8 ? 2 : 4;      // 4 wavefronts
+  p->MT = nmt <= 8 ? 1 : 2;  // bf16: 8 wavefronts, 1 or 2 m-tiles each
   p->ve = sh->dtype == SD_BF16 && nmt >= 7 && nmt <= 8;
+  p->part_rows = p->Mpad;
   size_t off = 0;
   p->off_ml = off;
   if (p->max_splits > 1) off = align256(off + (size_t)slots * p->Mpad * sizeof(float2));
   p->off_o = off;
   if (p->max_splits > 1) off = align256(off + (size_t)slots * p->Mpad * D * sizeof(float));
-  p->total = off > 0 ? off : 256;
+  p->total = p->min_total = off > 0 ? off : 256;
+  if (f32) {
+    // Balanced shares of the pairs' m-tile groups wherever that gives a CU more than whole pairs would:
+    // at most kBalGrid workgroups, whose slots are the workspace.
+    p->groups = (nmt + sdb::kF32GroupMT - 1) / sdb::kF32GroupMT;
+    p->group_mt = (nmt + p->groups - 1) / p->groups;
+    p->part_rows = p->group_mt * 16;
+    const long long tiles = (max_L + sdb::kF32KT - 1) / sdb::kF32KT;
+    p->bal = pairs > 0 && tiles > kBalMinTilesF32 && pairs * p->groups * tiles * sdb::kF32GroupMT <= (1LL << 30);
+    if (p->bal) p->total = std::max(p->min_total, f32_bytes(*p, pairs, D, kBalGrid));
+  }
   return ok();
 }
 
-template <bool BF16, int D, int MT>
-void launch_attn(const sdb::AttnArgs &a, int grid, hipStream_t st) {
-  hipLaunchKernelGGL((sdb::block_attn_kernel<BF16, D, MT>), dim3(grid), dim3(256), 0, st, a);
+// fp32: the split kernel, and the merge where pairs may be split.
+template <int D>
+void launch_attn_f32(const sdb::AttnArgs &a, hipStream_t st) {
+  // at most bal_grid splits wherever the pairs are fewer than about half of that (f32_item), else no
+  // more than one more per pair
+  const int pairs = a.S * a.Hkv * a.groups;
+  const int grid = a.bal ? (31 * pairs <= 15 * a.bal_grid ? a.bal_grid : a.bal_grid + pairs) : pairs;
+  hipLaunchKernelGGL((sdb::block_attn_f32_kernel<D>), dim3(grid), dim3(64 * sdb::kF32Waves), 0, st, a);
+  if (!a.bal) return;
+  constexpr int RB = 256 / (D / 4);
+  const int nrb = (a.Mpad + RB - 1) / RB;
+  const dim3 g(a.S * a.Hkv * nrb);
+  if (pairs * 8 >= a.bal_grid) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<false, D, 8>), g, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((sdb::block_attn_merge_kernel<false, D, 16>), g, dim3(256), 0, st, a);
 }
 
 // The balanced plan (bf16): kBalGrid workgroups, then the merge.
@@ -194,32 +233,26 @@ void launch_attn_bal(sdb::AttnArgs a, int MT, hipStream_t st, bool ve) {
   hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 8>), dim3(a.S * a.Hkv * nrb), dim3(256), 0, st, a);
 }
 
-template <bool BF16, int D, bool PAGED = false, bool APPEND = false>
-void launch_attn_all(const sdb::AttnArgs &a, int grid, int MT, hipStream_t st, bool ve = false) {
-  if constexpr (BF16) {
-    if (ve)
-      hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND, false, true>), dim3(grid),
-                         dim3(512), 0, st, a);
-    else if (MT == 1)
-      hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND>), dim3(grid), dim3(512), 0,
-                         st, a);
-    else
-      hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 2, kBf16KT, kBf16NS, PAGED, APPEND>), dim3(grid), dim3(512), 0,
-                         st, a);
-  } else {
-    if (MT == 1) launch_attn<BF16, D, 1>(a, grid, st);
-    else if (MT == 2) launch_attn<BF16, D, 2>(a, grid, st);
-    else launch_attn<BF16, D, 4>(a, grid, st);
-  }
+template <int D, bool PAGED = false, bool APPEND = false>
+void launch_attn_all(const sdb::AttnArgs &a, int grid, int MT, hipStream_t st, bool ve) {
+  if (ve)
+    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND, false, true>), dim3(grid),
+                       dim3(512), 0, st, a);
+  else if (MT == 1)
+    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND>), dim3(grid), dim3(512), 0,
+                       st, a);
+  else
+    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 2, kBf16KT, kBf16NS, PAGED, APPEND>), dim3(grid), dim3(512), 0,
+                       st, a);
   if (a.max_splits > 1) {
     constexpr int RB = 256 / (D / 4);  // rows per merge workgroup
     const int nrb = (a.Mpad + RB - 1) / RB;
     const dim3 g(a.S * a.Hkv * nrb);
     // every split's loads in one round where the plan allows up to 16 splits (Qwen3-4B verify at
     // batch 1, 9 splits per pair: merge kernel 5.34 -> 4.51 us)
-    if (a.max_splits <= 4) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<BF16, D, 4>), g, dim3(256), 0, st, a);
-    else if (a.max_splits <= 8) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<BF16, D, 8>), g, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((sdb::block_attn_merge_kernel<BF16, D, 16>), g, dim3(256), 0, st, a);
+    if (a.max_splits <= 4) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 4>), g, dim3(256), 0, st, a);
+    else if (a.max_splits <= 8) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 8>), g, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 16>), g, dim3(256), 0, st, a);
   }
 }
 
@@ -412,7 +445,7 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(out))
     return fail(SD_ERR_INVALID_ARG, "q, caches and out must be 16-byte aligned");
   if (((uintptr_t)workspace & 255u) != 0) return fail(SD_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-  if (workspace_bytes < p.total)
+  if (workspace_bytes < p.min_total)
     return fail(SD_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, p.total);
   a->q = q;
   a->k = k_cache;
@@ -424,6 +457,24 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
   char *ws = (char *)workspace;
   a->part_ml = (float2 *)(ws + p.off_ml);
   a->part_o = (float *)(ws + p.off_o);
+  a->bal = 0;  // bf16: the calls turn it on where the plan says so
+  a->bal_grid = p.bal_grid;
+  a->group_mt = a->groups = 0;
+  a->plan = nullptr;
+  a->part_rows = p.part_rows;
+  if (sh->dtype == SD_F32) {
+    a->group_mt = p.group_mt;
+    a->groups = p.groups;
+    // as many workgroups as the workspace has slots for; none: whole pairs
+    const long long pairs = (long long)sh->num_seqs * sh->num_kv_heads;
+    long long grid = p.bal ? kBalGrid : 0;
+    while (grid > 0 && f32_bytes(p, pairs, sh->head_dim, grid) > workspace_bytes) --grid;
+    a->bal = grid > 0;
+    a->bal_grid = (int)grid;
+    const size_t rows = (size_t)(grid + pairs * p.groups) * p.part_rows;
+    a->part_o = (float *)(ws + align256(rows * sizeof(float2)));
+    a->plan = (int *)((char *)a->part_o + align256(rows * sh->head_dim * sizeof(float)));
+  }
   a->S = sh->num_seqs;
   a->Hq = sh->num_q_heads;
   a->Hkv = sh->num_kv_heads;
@@ -442,10 +493,8 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
   a->block_table = nullptr;
   a->page_log2 = a->max_pages = a->num_pages = 0;
   a->k_new = a->v_new = nullptr;
-  a->bal = 0;  // sd_block_attn turns it on where its plan says so
-  a->bal_grid = kBalGrid;
-  a->bal_min_tiles = kBalMinTiles;
-  a->bal_kt = kBf16KT;
+  a->bal_min_tiles = sh->dtype == SD_BF16 ? kBalMinTiles : kBalMinTilesF32;
+  a->bal_kt = sh->dtype == SD_BF16 ? kBf16KT : sdb::kF32KT;
   return ok();
 }
 
@@ -466,20 +515,17 @@ int sd_block_attn(const sd_attn_shape *sh, const void *q, const void *k_cache, c
   rc = attn_args(sh, p, q, k_cache, v_cache, ctx_lens, block_lens, q_offsets, mask_mode, out, workspace,
                  workspace_bytes, &a);
   if (rc) return rc;
-  const int grid = p.grid;
   hipStream_t st = (hipStream_t)stream;
-  const bool bf = sh->dtype == SD_BF16;
-  if (p.bal) {
-    if (sh->head_dim == 128) launch_attn_bal<128>(a, p.MT, st, p.ve);
+  const bool d128 = sh->head_dim == 128;
+  if (sh->dtype == SD_F32) {
+    if (d128) launch_attn_f32<128>(a, st);
+    else launch_attn_f32<64>(a, st);
+  } else if (p.bal) {
+    if (d128) launch_attn_bal<128>(a, p.MT, st, p.ve);
     else launch_attn_bal<64>(a, p.MT, st, p.ve);
-    return check_launch("sd_block_attn");
-  }
-  if (sh->head_dim == 128) {
-    if (bf) launch_attn_all<true, 128>(a, grid, p.MT, st, p.ve);
-    else launch_attn_all<false, 128>(a, grid, p.MT, st);
   } else {
-    if (bf) launch_attn_all<true, 64>(a, grid, p.MT, st, p.ve);
-    else launch_attn_all<false, 64>(a, grid, p.MT, st);
+    if (d128) launch_attn_all<128>(a, p.grid, p.MT, st, p.ve);
+    else launch_attn_all<64>(a, p.grid, p.MT, st, p.ve);
   }
   return check_launch("sd_block_attn");
 }
@@ -509,9 +555,9 @@ int sd_block_attn_append(const sd_attn_shape *sh, const void *q, const void *k_n
     if (sh->head_dim == 128) launch_attn_bal<128, false, true>(a, p.MT, st, p.ve);
     else launch_attn_bal<64, false, true>(a, p.MT, st, p.ve);
   } else if (sh->head_dim == 128) {
-    launch_attn_all<true, 128, false, true>(a, p.grid, p.MT, st, p.ve);
+    launch_attn_all<128, false, true>(a, p.grid, p.MT, st, p.ve);
   } else {
-    launch_attn_all<true, 64, false, true>(a, p.grid, p.MT, st, p.ve);
+    launch_attn_all<64, false, true>(a, p.grid, p.MT, st, p.ve);
   }
   return check_launch("sd_block_attn_append");
 }
@@ -560,9 +606,9 @@ int sd_block_attn_paged(const sd_attn_shape *sh, int32_t page_size, int32_t num_
     if (sh->head_dim == 128) launch_attn_bal<128, true>(a, p.MT, st, p.ve);
     else launch_attn_bal<64, true>(a, p.MT, st, p.ve);
   } else if (sh->head_dim == 128) {
-    launch_attn_all<true, 128, true>(a, grid, p.MT, st, p.ve);
+    launch_attn_all<128, true>(a, grid, p.MT, st, p.ve);
   } else {
-    launch_attn_all<true, 64, true>(a, grid, p.MT, st, p.ve);
+    launch_attn_all<64, true>(a, grid, p.MT, st, p.ve);
   }
   return check_launch("sd_block_attn_paged");
 }
@@ -1014,8 +1060,12 @@ int sd_verify_step(const sd_attn_shape *ash, int32_t num_layers, const sd_layer_
       return fail(SD_ERR_INVALID_ARG, "sd_verify_step: layer %d buffers must be 16-byte aligned", l);
   }
   size_t need = 0;
-  int rc = sd_verify_step_workspace_size(ash, csh, temperature, &need);
+  int rc = sd_accept_workspace_size(csh, temperature, &need);
   if (rc) return rc;
+  AttnPlan ap;
+  rc = attn_plan(ash, &ap);
+  if (rc) return rc;
+  need = std::max(need, ap.min_total);  // the attention calls fit their plan to a smaller workspace
   if (workspace_bytes < need) return fail(SD_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
   // the acceptance and commit arguments too, before the layers are enqueued
   AcceptPlan cp;

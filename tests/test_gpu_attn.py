@@ -276,3 +276,34 @@ def test_balanced_two_mtiles_per_wavefront(mode):
     p = W.make_attn(rs, S=S, Hq=16, Hkv=2, D=64, ctx_lens=ctx, block_lens=B, dtype="bf16", mask_mode=mode,
                     name="bal_two_mtiles")
     _attn_with_bounds(p, p.max_ctx, p.max_block)
+
+
+def _f32(seed, S, Hq, Hkv, D, ctx, B, mask):
+    rs = W._streams(seed)
+    return W.make_attn(rs, S=S, Hq=Hq, Hkv=Hkv, D=D, ctx_lens=ctx, block_lens=B, dtype="f32", mask_mode=mask,
+                       name=f"f32_{S}_{Hq}_{Hkv}_{D}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,Hq,Hkv,ctx,B,mask", [
+    (1, 1, 1, [0], [1], CAUSAL),                                # one key, one row
+    (3, 4, 1, [63, 0, 128], [1, 64, 4], BIDIR),                 # 64-key tiles: short by none, one tile, one past
+    (2, 8, 1, [47, 240], [32, 9], CAUSAL),                      # 16 m-tiles (four groups of four) beside 5
+    (4, 10, 2, [300, 17, 65, 511], [13, 26, 0, 1], CAUSAL),     # 5 and 9 m-tiles (two and three groups), an empty block
+    (70, 2, 1, [(37 * i) % 400 for i in range(70)], [1 + i % 9 for i in range(70)], BIDIR),  # two rounds of 64 sequences
+    (40, 8, 8, [(53 * i) % 300 for i in range(40)], [i % 5 for i in range(40)], CAUSAL),     # more pairs than CUs
+])
+def test_f32_plan_edges(S, Hq, Hkv, D, ctx, B, mask):
+    """Every row of the fp32 plan's edges at the fp32 tolerance, and again with a workspace of the even
+    splits' size, which leaves fewer slots or none (whole pairs)."""
+    p = _f32(7 + S, S, Hq, Hkv, D, ctx, B, mask)
+    G.check_attn(p)
+    pairs, L, mpad = S * Hkv, p.max_ctx + p.max_block, -(-(Hq // Hkv) * p.max_block // 16) * 16
+    up = lambda n, m: -(-n // m) * m
+    sl = max(256, min(4096, up(-(-L // max(1, 512 // pairs)), 32)))
+    n = -(-L // sl)
+    need = up(pairs * n * mpad * 8, 256) + up(pairs * n * mpad * D * 4, 256) if n > 1 else 256
+    full = G.run_attn(p).cpu()
+    small = G.run_attn(p, workspace=torch.empty(need, dtype=torch.uint8, device=G.dev())).cpu()
+    # each within 1e-5 of the oracle
+    assert (full - small).abs().max().item() <= 2e-5
