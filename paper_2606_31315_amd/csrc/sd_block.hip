@@ -1224,13 +1224,8 @@ int sd_survival_tau(const sd_survival_shape *sh, const float *gamma, const int32
   a.b_star = b_star;
   a.regret = regret;
   a.lipschitz = lipschitz;
-  // samples per workgroup: the most of 256, 128, 64 whose staged rows fit the LDS budget
-  const size_t row_bytes = (size_t)(a.P + 1) * sizeof(float), fixed = sdb::kSurvMaxCands * sizeof(double);
-  int spw = 256;
-  while (spw > 64 && fixed + spw * row_bytes > (size_t)sdb::kSurvLdsBytes) spw /= 2;
-  const size_t lds = fixed + spw * row_bytes;
-  const int grid = (a.N + spw - 1) / spw;
-  hipLaunchKernelGGL(sdb::survival_tau_kernel, dim3(grid), dim3(spw), lds, (hipStream_t)stream, a);
+  const int grid = (int)(((long long)a.N + 63) / 64);
+  hipLaunchKernelGGL(sdb::survival_tau_kernel, dim3(grid), dim3(64), sdb::tau_lds(a.P, a.C), (hipStream_t)stream, a);
   return check_launch("sd_survival_tau");
 }
 

@@ -7,9 +7,9 @@
 // App. A.3: the regret of a predicted size is R(x) = tau(B*(x)) - tau(B_hat(x)), bounded by
 // L_tau |B* - B_hat| for the discrete Lipschitz constant L_tau of tau over the candidates.
 //
-//   survival_tau_kernel     one thread per sample: tau for every candidate, B*, the regret of
-//                           B_hat and L_tau.  A workgroup stages its samples' gamma rows
-//                           through LDS so the HBM reads are contiguous 16-byte vectors.
+//   survival_tau_kernel     one lane per sample: tau for every candidate, B*, the regret of
+//                           B_hat and L_tau.  A wavefront stages its samples' gamma rows and
+//                           their tau through LDS so the HBM accesses are contiguous.
 //   survival_sample_kernel  Monte Carlo of L_b(x): a wavefront (or a workgroup, where pairs are few)
 //                           per (sample, candidate), one trial per lane, the next one as soon as
 //                           it ends.  Uniforms come from Philox4x64-10 (Salmon
@@ -20,13 +20,14 @@
 // fp64 throughout: gamma (fp32) widens exactly, the products and sums are fp64.
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace sdb {
 
 constexpr int kSurvMaxCands = 64;
 constexpr int kSurvMaxPos = 128;
-constexpr int kSurvLdsBytes = 65536;  // staging budget of survival_tau_kernel
 
 struct SurvivalArgs {
   const float *gamma;   // [N, P]
@@ -48,79 +49,176 @@ __device__ __forceinline__ double retention(int b, int B, double alpha) {
   return exp(-alpha * d * d);
 }
 
-// One thread per sample, blockDim.x samples per workgroup (64, 128 or 256, so that the
-// staged rows fit 64 KB of LDS).  Dynamic LDS: C retention factors (doubles), then the gamma
-// rows, row stride P + 1 floats (odd, so a wavefront's per-thread row reads fall in distinct
-// banks).
-__global__ __launch_bounds__(256) void survival_tau_kernel(SurvivalArgs a) {
-  extern __shared__ __attribute__((aligned(16))) double r_lds[];
-  const int P = a.P, C = a.C, stride = P + 1;
-  float *lds = reinterpret_cast<float *>(r_lds + kSurvMaxCands);
-  const int tid = threadIdx.x, spw = blockDim.x;
-  const long long n0 = (long long)blockIdx.x * spw;
-  const int rows = (int)min((long long)spw, (long long)a.N - n0);
-  // the workgroup's rows are one contiguous run of rows * P floats; 16-byte loads when P % 4 == 0
+// One wavefront per workgroup, one sample per lane: no barrier joins one wavefront's loads to
+// another's arithmetic, and the LDS of a CU holds 18 of them at 32 positions.  The samples' gamma rows
+// are one contiguous run, read as 16-byte vectors (every load of 8 KB in flight at once) into LDS rows of
+// odd stride, so that the lanes' row reads fall in distinct banks.  Up to kTauCands candidates
+// are carried through one pass over the row, as many independent chains of products as there are;
+// their tau go out through LDS, so that the stores are contiguous.
+// 2^20 samples x 32 positions x 5 candidates (201 MB): 256 threads with a barrier, one candidate's
+// chain at a time and strided stores 47.1 us; this 39.6 us, 5.1 TB/s, the rate of a copy.  On the way
+// 46.1 us with every position tested against each candidate's size past the first, 42.5 with a
+// division only where candidates are not neighbours and non-temporal accesses, 39.6 with the positions
+// between two sizes run for the remaining candidates alone.
+constexpr int kTauCands = 8;
+
+// Dynamic LDS: the gamma rows, and the tau of a pass (where one pass takes every candidate, in
+// their place).
+__host__ __device__ inline int tau_rows_bytes(int P) { return 64 * ((P + 1) | 1) * (int)sizeof(float); }
+__host__ __device__ inline int tau_lds(int P, int C) {
+  const int rows = (tau_rows_bytes(P) + 15) & ~15, out = 64 * (C < kTauCands ? C : kTauCands) * (int)sizeof(double);
+  return C <= kTauCands ? (rows > out ? rows : out) : rows + out;
+}
+
+struct TauState {
+  double best, prev, lip, hat;
+  int best_b, prev_b;
+  bool found;
+};
+
+// Candidates c0 .. c0 + NC - 1 of the lane's sample (row g): tau into t, r their retention factors.
+template <int NC>
+__device__ __forceinline__ void tau_pass(const SurvivalArgs &a, const float *g, int c0, double r_lane, int bh,
+                                         TauState &st, double (&t)[kTauCands]) {
+  double r[NC], prod[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    r[c] = readlane_d(r_lane, c0 + c);
+    prod[c] = 1.0;
+    t[c] = 0.0;
+  }
+  // prod_{j<=i+1} q_j of every candidate; sizes ascend, so candidate c - 1 is done where c goes on
+  int i = 0;
+  auto steps = [&](auto from_c, auto count_c) {  // positions i .. of candidates from_c and up
+    constexpr int F = decltype(from_c)::value, K = decltype(count_c)::value;
+    float x[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) x[k] = g[i + k];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const double gd = (double)x[k];
+#pragma unroll
+      for (int c = F; c < NC; ++c) {
+        prod[c] *= gd * r[c];
+        t[c] += prod[c];
+      }
+    }
+    i += K;
+  };
+  auto runs = [&](auto from_c) {
+    const int n = a.cands[c0 + decltype(from_c)::value];
+    while (i + 4 <= n) steps(from_c, std::integral_constant<int, 4>{});
+    while (i < n) steps(from_c, std::integral_constant<int, 1>{});
+  };
+  runs(std::integral_constant<int, 0>{});
+  if constexpr (NC > 1) runs(std::integral_constant<int, (NC > 1 ? 1 : 0)>{});
+  if constexpr (NC > 2) runs(std::integral_constant<int, (NC > 2 ? 2 : 0)>{});
+  if constexpr (NC > 3) runs(std::integral_constant<int, (NC > 3 ? 3 : 0)>{});
+  if constexpr (NC > 4) runs(std::integral_constant<int, (NC > 4 ? 4 : 0)>{});
+  if constexpr (NC > 5) runs(std::integral_constant<int, (NC > 5 ? 5 : 0)>{});
+  if constexpr (NC > 6) runs(std::integral_constant<int, (NC > 6 ? 6 : 0)>{});
+  if constexpr (NC > 7) runs(std::integral_constant<int, (NC > 7 ? 7 : 0)>{});
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int b = a.cands[c0 + c];
+    if (t[c] > st.best) {  // strict: ties keep the smaller block size
+      st.best = t[c];
+      st.best_b = b;
+    }
+    // A chord's slope over non-adjacent candidates is a weighted mean of the adjacent slopes
+    // it spans, so the largest slope over all pairs is the largest over adjacent pairs.
+    if (c0 + c > 0) {
+      const double d = fabs(t[c] - st.prev);
+      const int gap = b - st.prev_b;  // uniform; a division only where there is one to make
+      st.lip = fmax(st.lip, gap == 1 ? d : d / (double)gap);
+    }
+    if (b == bh) {
+      st.hat = t[c];
+      st.found = true;
+    }
+    st.prev = t[c];
+    st.prev_b = b;
+  }
+}
+
+__global__ __launch_bounds__(64) void survival_tau_kernel(SurvivalArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char tau_smem[];
+  const int P = a.P, C = a.C, stride = (P + 1) | 1;
+  float *lds = reinterpret_cast<float *>(tau_smem);
+  double *out = reinterpret_cast<double *>(tau_smem + (C <= kTauCands ? 0 : (tau_rows_bytes(P) + 15) & ~15));
+  const int lane = threadIdx.x;
+  const long long n0 = (long long)blockIdx.x * 64;
+  const int rows = (int)min(64LL, (long long)a.N - n0);
+  const int bh = (a.b_hat && lane < rows) ? a.b_hat[n0 + lane] : -1;
+  // the rows are one contiguous run of rows * P floats; 16-byte loads when P % 4 == 0
   const float *src = a.gamma + n0 * P;
   const int total = rows * P;
   if ((P & 3) == 0) {
-    // batches of 8 vectors per thread, every load of a batch issued before any LDS store
-    const float4 *s4 = reinterpret_cast<const float4 *>(src);
+    const f32x4 *s4 = reinterpret_cast<const f32x4 *>(src);
     const int nvec = total / 4;
-    for (int v0 = tid; v0 < nvec; v0 += 8 * spw) {
-      float4 x[8];
+    // element 4 v of the run is (row, col); 64 vectors on, it moves by dr rows and dc columns
+    const int dr = 256 / P, dc = 256 - dr * P;
+    int row = (4 * lane) / P, col = 4 * lane - row * P;
+    for (int v0 = lane; v0 < nvec; v0 += 8 * 64) {
+      f32x4 x[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = s4[min(v0 + k * spw, nvec - 1)];  // clamped: no per-load branch
+      for (int k = 0; k < 8; ++k) {  // clamped: no per-load branch
+        const f32x4 *p = s4 + min(v0 + k * 64, nvec - 1);
+        x[k] = __builtin_nontemporal_load(p);
+      }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int v = v0 + k * spw;
-        if (v < nvec) {
-          const int e = 4 * v, row = e / P, col = e % P;  // P % 4 == 0: the 4 floats share a row
-          float *d = lds + row * stride + col;
-          d[0] = x[k].x;
-          d[1] = x[k].y;
-          d[2] = x[k].z;
-          d[3] = x[k].w;
+        if (v0 + k * 64 < nvec) {
+          float *d = lds + row * stride + col;  // P % 4 == 0: the 4 floats share a row
+          d[0] = x[k][0];
+          d[1] = x[k][1];
+          d[2] = x[k][2];
+          d[3] = x[k][3];
+        }
+        row += dr;
+        col += dc;
+        if (col >= P) {
+          col -= P;
+          ++row;
         }
       }
     }
   } else {
-    for (int e = tid; e < total; e += spw) lds[(e / P) * stride + e % P] = src[e];
+    for (int e = lane; e < total; e += 64) lds[(e / P) * stride + e % P] = src[e];
   }
-  if (tid < C) r_lds[tid] = retention(a.cands[tid], a.train_block, a.alpha);
+  const double r_lane = retention(a.cands[min(lane, C - 1)], a.train_block, a.alpha);
   __syncthreads();
-  if (tid >= rows) return;
-  const long long n = n0 + tid;
-  const float *g = lds + tid * stride;
-  double best_tau = -1.0, prev_tau = 0.0, lip = 0.0, hat_tau = 0.0;
-  int best_b = a.cands[0], prev_b = 0;
-  const int bh = a.b_hat ? a.b_hat[n] : -1;
-  bool hat_found = false;
-  for (int c = 0; c < C; ++c) {
-    const int b = a.cands[c];
-    const double r = r_lds[c];
-    double prod = 1.0, t = 0.0;
-    for (int i = 0; i < b; ++i) {
-      prod *= (double)g[i] * r;  // prod_{j<=i+1} q_j
-      t += prod;
+  const float *g = lds + min(lane, rows - 1) * stride;
+  TauState st{-1.0, 0.0, 0.0, 0.0, a.cands[0], 0, false};
+  for (int c0 = 0; c0 < C; c0 += kTauCands) {
+    const int nc = min(C - c0, kTauCands);
+    double t[kTauCands];
+    switch (nc) {  // uniform
+      case 1: tau_pass<1>(a, g, c0, r_lane, bh, st, t); break;
+      case 2: tau_pass<2>(a, g, c0, r_lane, bh, st, t); break;
+      case 3: tau_pass<3>(a, g, c0, r_lane, bh, st, t); break;
+      case 4: tau_pass<4>(a, g, c0, r_lane, bh, st, t); break;
+      case 5: tau_pass<5>(a, g, c0, r_lane, bh, st, t); break;
+      case 6: tau_pass<6>(a, g, c0, r_lane, bh, st, t); break;
+      case 7: tau_pass<7>(a, g, c0, r_lane, bh, st, t); break;
+      default: tau_pass<8>(a, g, c0, r_lane, bh, st, t); break;
     }
-    a.tau[n * C + c] = t;
-    if (t > best_tau) {  // strict: ties keep the smaller block size
-      best_tau = t;
-      best_b = b;
+    __syncthreads();  // the rows are read (their place is reused where this is the only pass)
+#pragma unroll
+    for (int c = 0; c < kTauCands; ++c)
+      if (c < nc) out[lane * nc + c] = t[c];
+    __syncthreads();
+    for (int f = lane; f < rows * nc; f += 64) {
+      const long long o = C <= kTauCands ? n0 * C + f : (n0 + f / nc) * C + c0 + f % nc;
+      __builtin_nontemporal_store(out[f], a.tau + o);
     }
-    // A chord's slope over non-adjacent candidates is a weighted mean of the adjacent slopes
-    // it spans, so the largest slope over all pairs is the largest over adjacent pairs.
-    if (c > 0) lip = fmax(lip, fabs(t - prev_tau) / (double)(b - prev_b));
-    if (b == bh) {
-      hat_tau = t;
-      hat_found = true;
-    }
-    prev_tau = t;
-    prev_b = b;
+    __syncthreads();  // before the next pass writes out
   }
-  a.b_star[n] = best_b;
-  if (a.lipschitz) a.lipschitz[n] = lip;
-  if (a.regret) a.regret[n] = hat_found ? best_tau - hat_tau : __builtin_nan("");
+  if (lane >= rows) return;
+  const long long n = n0 + lane;
+  a.b_star[n] = st.best_b;
+  if (a.lipschitz) a.lipschitz[n] = st.lip;
+  if (a.regret) a.regret[n] = st.found ? st.best - st.hat : __builtin_nan("");
 }
 
 // ---- Philox4x64-10 ----

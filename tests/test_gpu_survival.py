@@ -66,6 +66,18 @@ def test_tau_64_candidates_128_positions():
     _tau_check(p)
 
 
+@pytest.mark.parametrize("N,P,cands", [(1, 1, [1]), (63, 7, [1, 7]), (64, 16, [3, 4, 9]), (65, 33, [4, 8, 12, 33]),
+                                       (130, 32, [1, 2, 3, 5, 8, 13, 21, 32]), (67, 40, [2, 6, 7, 11, 15, 16, 18, 30, 40]),
+                                       (66, 128, list(range(8, 129, 8)))])
+def test_tau_candidate_passes(N, P, cands):
+    """One candidate to two full passes of eight, neighbours and gaps of every length mod 4, positions a
+    multiple of four or not, and samples on both sides of a wavefront."""
+    p = W.make_survival(37, N=N, P=P, train_block=max(1, P // 2), radius=0, alpha=0.003)
+    p.cands = np.array(cands, dtype=np.int32)
+    p.b_hat = p.cands[np.arange(N) % len(cands)].astype(np.int32)
+    _tau_check(p)
+
+
 def test_tau_degenerate_cases():
     p = W.make_survival(34, N=70, P=16, train_block=8, radius=3, alpha=0.05)
     p.gamma[:10] = 0.0                    # every tau 0: B* is the smallest candidate
