@@ -201,9 +201,9 @@ int sd_accept_workspace_size(const sd_accept_shape *shape, float temperature, si
  *   T = 0: one launch (at most 8 statistics chunks of 32768 bf16 / 16384 fp32 logits per row,
  *          at most 1024 sequences) instead of two;
  *   T > 0: two launches instead of three (rows of at most 256 sampling chunks of 256 16-byte
- *          vectors, i.e. 524288 bf16 / 262144 fp32 logits, and the num_seqs x chunks
- *          workgroups of the second launch resident at once with a quarter of the device to
- *          spare).
+ *          vectors, i.e. 524288 bf16 / 262144 fp32 logits, and the workgroups of the second
+ *          launch, one per sequence and chunk or else four chunks, resident at once with a
+ *          quarter of the device to spare).
  * Every path gives identical results.  The single launches need their waiting workgroups
  * resident; a wait that gives up (after about a second, e.g. when other work holds the device)
  * writes -1: at T = 0 its sequence reports -1 in accept_len and next_token, at T > 0 in one or

@@ -33,7 +33,8 @@
 //   accept_fused_kernel     T = 0 in one launch: the statistics items, then one workgroup per
 //                           sequence that waits for its records (tagged words) and decides.
 //   accept_draw_kernel      T > 0, the mass and locate steps in one launch: the chunk sums are
-//                           handed between the workgroups of a sequence as tagged words.
+//                           handed between the workgroups of a sequence as tagged words
+//                           (accept_draw_multi_kernel: several chunks per workgroup).
 // The single launches run where the shape, the workspace and the stream allow them; the
 // launches above stay for the other cases and give the same results bit for bit.
 #pragma once
@@ -119,7 +120,9 @@ struct RowChunk {
   int e0, e1;        // the chunk's contiguous relative range
 };
 
-template <int VEC>
+// SMALL: at most 256 chunks of at most 256 vectors, whose boundaries take 32-bit divisions (the 64-bit
+// ones are some hundred scalar instructions each, between the decision and the row's loads).
+template <int VEC, bool SMALL = false>
 __device__ __forceinline__ RowChunk row_chunk(long long a0, int V, int c, int nch) {
   RowChunk r;
   const long long o0 = (a0 + VEC - 1) / VEC, o1 = (a0 + V) / VEC;
@@ -134,8 +137,14 @@ __device__ __forceinline__ RowChunk row_chunk(long long a0, int V, int c, int nc
     return r;
   }
   const long long nv = o1 - o0;
-  r.vb = o0 + nv * c / nch;
-  r.ve = o0 + nv * (c + 1) / nch;
+  if constexpr (SMALL) {
+    const unsigned n = (unsigned)nv;
+    r.vb = o0 + n * (unsigned)c / (unsigned)nch;
+    r.ve = o0 + n * (unsigned)(c + 1) / (unsigned)nch;
+  } else {
+    r.vb = o0 + nv * c / nch;
+    r.ve = o0 + nv * (c + 1) / nch;
+  }
   r.hb = 0;
   r.he = (c == 0) ? (int)(o0 * VEC - a0) : 0;
   r.tb = (int)(o1 * VEC - a0);
@@ -1216,7 +1225,7 @@ __global__ __launch_bounds__(256, 4) void accept_draw_kernel(AcceptArgs a) {
   const SampleParams sp{si0.z, si0.w, si1.x, si1.y, a.c};
   const long long ta0 = (long long)(off + j) * a.V;
   const long long da0 = (long long)(off - s + j) * a.V;  // read only at a rejection
-  const RowChunk ch = row_chunk<VEC>(ta0, a.V, c, a.nch2);
+  const RowChunk ch = row_chunk<VEC, true>(ta0, a.V, c, a.nch2);
   const bool dvec = ((ta0 - da0) % VEC) == 0;
   const int nvc = (int)(ch.ve - ch.vb);  // <= 256: one vector per thread
   const bool has = tid < nvc;
@@ -1376,6 +1385,222 @@ __global__ __launch_bounds__(256, 4) void accept_draw_kernel(AcceptArgs a) {
       if (has) step(eb + i, mm[i]);
     if (tid == kLocThreads - 1)
       for (int e = ch.tb; e < ch.te; ++e) step(e, use_q ? sh_em[1][0][e - ch.tb] : sh_em[1][1][e - ch.tb]);
+    a.next_token[s] = found >= 0 ? found : elast;  // rounding: the run's last token with mass
+    a.accept_len[s] = j;
+    sh_hit = 1;
+  }
+  __syncthreads();
+  if (tid == 0 && !sh_hit) {  // rounding: the chunk's last token with mass (0 if none)
+    int t = -1;
+    for (int w2 = 0; w2 < NW; ++w2) t = max(t, sh_last[w2]);
+    a.next_token[s] = max(t, 0);
+    a.accept_len[s] = j;
+  }
+}
+
+// The same with kDrawChunks sampling chunks per workgroup, for batches whose chunks number more than
+// the workgroups the device holds at once: grid = (sequence, group of consecutive chunks).  Every
+// chunk's sums are made and filed as above, all of a workgroup's loads in flight together; the
+// workgroup that owns the chosen chunk then takes that chunk's masses again from the vectors it
+// kept, and scans and walks it as above.  Results agree bit for bit.  32 sequences at V = 151936 (2400
+// chunks, 608 workgroups), T = 1: 12.8 us against 10.4 + 4.8 for the mass and locate launches, 61.2 us per
+// call against 63.0; what is left over a chunk per workgroup's 7.7 us is the rows' 19 MB.
+constexpr int kDrawChunks = 4;
+
+template <bool BF16>
+__global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a) {
+  constexpr int VEC = BF16 ? 8 : 4, NW = 4, K = kDrawChunks;
+  __shared__ float4 sh_si[2];
+  __shared__ double sh_r[K][NW], sh_p[K][NW], sh_w[NW];
+  __shared__ float sh_em[2][2][2 * VEC];  // [head, tail][residual, p] masses of the scalar elements
+  __shared__ double sh_cex, sh_tgt;
+  __shared__ int sh_kc, sh_usep, sh_ok, sh_hit, sh_last[NW];
+  const int ngrp = (a.nch2 + K - 1) / K;
+  const int s = blockIdx.x / ngrp, grp = blockIdx.x - s * ngrp, c0 = grp * K;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int B = ld_uniform(a.block_lens, s);
+  const int off = ld_uniform(a.q_offsets, s);
+  mass_decide(a, s, B, sh_si, false);
+  __syncthreads();
+  const float4 si0 = sh_si[0], si1 = sh_si[1];
+  const int j = __float_as_int(si0.x);
+  const bool residual = si0.y != 0.f;
+  const SampleParams sp{si0.z, si0.w, si1.x, si1.y, a.c};
+  const long long ta0 = (long long)(off + j) * a.V;
+  const long long da0 = (long long)(off - s + j) * a.V;  // read only at a rejection
+  const bool dvec = ((ta0 - da0) % VEC) == 0;
+
+  // ---- every chunk's vector of this thread, loaded together ----
+  u32x4 tb[K], qb[K];
+  RowChunk chs[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    tb[k] = qb[k] = u32x4{0u, 0u, 0u, 0u};
+    const RowChunk ch = chs[k] = row_chunk<VEC, true>(ta0, a.V, min(c0 + k, a.nch2 - 1), a.nch2);
+    const int nvc = (int)(ch.ve - ch.vb);  // <= 256: one vector per thread
+    if (nvc > 0) {  // clamped: no per-load branch
+      const unsigned r = (unsigned)min(tid, nvc - 1);
+      tb[k] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.target) + (ch.vb + r) * 16);
+      if (residual && dvec)
+        qb[k] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.draft) +
+                                                 (ch.vb + r + (da0 - ta0) / VEC) * 16);
+    }
+  }
+  // masses of this thread's vector of chunk c: accept_mass_kernel's, element by element
+  auto masses = [&](const RowChunk &ch, const u32x4 &tv, const u32x4 &qv, float (&mr)[VEC], float (&mp)[VEC]) {
+    float t[VEC], q[VEC];
+    unpack<BF16>(tv, t);
+    unpack<BF16>(qv, q);
+    if (residual && !dvec && tid < (int)(ch.ve - ch.vb)) {
+      const long long e = (ch.vb + tid) * VEC - ta0 + da0;
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) q[i] = load_elem<BF16>(a.draft, e + i);
+    }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) elem_masses(t[i], q[i], sp, residual, mr[i], mp[i]);
+  };
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int c = c0 + k;
+    if (c >= a.nch2) break;  // uniform
+    const RowChunk ch = chs[k];
+    float mr[VEC], mp[VEC], sr = 0.f, spm = 0.f, vr = 0.f, vp = 0.f;
+    masses(ch, tb[k], qb[k], mr, mp);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      vr += mr[i];
+      vp += mp[i];
+    }
+    if (tid < (int)(ch.ve - ch.vb)) {
+      sr += vr;
+      spm += vp;
+    }
+    // scalar head (chunk 0) and tail (last chunk): fewer than 2 * VEC elements each, one per thread
+    auto scalars = [&](int b, int e1, int which) {
+      for (int e = b + tid; e < e1; e += 256) {
+        float er, ep;
+        elem_masses(load_elem<BF16>(a.target, ta0 + e), residual ? load_elem<BF16>(a.draft, da0 + e) : 0.f, sp,
+                    residual, er, ep);
+        sr += er;
+        spm += ep;
+        if (e - b < 2 * VEC) {
+          sh_em[which][0][e - b] = er;
+          sh_em[which][1][e - b] = ep;
+        }
+      }
+    };
+    scalars(ch.hb, ch.he, 0);
+    scalars(ch.tb, ch.te, 1);
+    const float wr = wave_sum_f(sr), wp = wave_sum_f(spm);
+    if (lane == 0) {
+      sh_r[k][wave] = wr;
+      sh_p[k][wave] = wp;
+    }
+  }
+  __syncthreads();
+  static_assert(K * 2 * kSumReplicas <= 256, "one word of one copy of one chunk per thread");
+  if (tid < K * 2 * kSumReplicas) {
+    const int k = tid / (2 * kSumReplicas), w = tid & 1, r = (tid >> 1) % kSumReplicas;
+    if (c0 + k < a.nch2) {
+      const double *x = w ? sh_p[k] : sh_r[k];
+      tag_put(a.csum + ((size_t)(s * kSumReplicas + r) * 2 + w) * a.nch2 + c0 + k, a.tag + (unsigned)w * kTagStep,
+              __float_as_uint((float)(x[0] + x[1] + x[2] + x[3])));
+    }
+  }
+
+  // ---- every chunk sum of the sequence, then the chunk search ----
+  if (wave == 0) {
+    double2 cm[kLocSums];
+    const bool ok = poll_chunk_sums_n(a, s, grp % kSumReplicas, cm);
+    if (ok) {
+      const ChunkPick cp = chunk_search([&](int k) { return pick_sums(cm, k); }, (a.nch2 + 63) / 64,
+                                        (double)si1.z);
+      if (lane == 0) {
+        sh_kc = cp.kc;
+        sh_cex = cp.cex;
+        sh_tgt = cp.tgt;
+        sh_usep = cp.use_p;
+      }
+    }
+    if (lane == 0) {
+      sh_ok = ok;
+      sh_hit = 0;
+    }
+  }
+  __syncthreads();
+  if (!sh_ok) {
+    if (tid == 0) {
+      a.accept_len[s] = -1;
+      a.next_token[s] = -1;
+    }
+    return;
+  }
+  const int kc = sh_kc, kk = kc - c0;
+  if (kk < 0 || kk >= K) return;
+
+  // ---- the chosen chunk: its masses again, their prefixes, and the walk ----
+  const bool use_q = residual && !sh_usep;
+  RowChunk ch = chs[0];
+  u32x4 tv = tb[0], qv = qb[0];
+#pragma unroll
+  for (int k = 1; k < K; ++k)
+    if (k == kk) {  // uniform
+      ch = chs[k];
+      tv = tb[k];
+      qv = qb[k];
+    }
+  const bool has = tid < (int)(ch.ve - ch.vb);
+  float mr[VEC], mp[VEC], mm[VEC];
+  masses(ch, tv, qv, mr, mp);
+  const int eb = (int)((ch.vb + tid) * VEC - ta0);
+  const float *em_h = sh_em[0][use_q ? 0 : 1], *em_t = sh_em[1][use_q ? 0 : 1];
+  double own = 0.0;
+  int elast = -1;
+  if (tid == 0)
+    for (int e = ch.hb; e < ch.he; ++e) {
+      const float m = em_h[e - ch.hb];
+      own += (double)m;
+      if (m > 0.f) elast = e;
+    }
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) {
+    const float m = has ? (use_q ? mr[i] : mp[i]) : 0.f;
+    mm[i] = m;
+    own += (double)m;
+    if (m > 0.f) elast = eb + i;
+  }
+  if (tid == kLocThreads - 1)
+    for (int e = ch.tb; e < ch.te; ++e) {
+      const float m = em_t[e - ch.tb];
+      own += (double)m;
+      if (m > 0.f) elast = e;
+    }
+  double ex;
+  const double in = wave_scan_d(own, &ex);
+  const int wl = wave_max_i(elast);
+  if (lane == 63) sh_w[wave] = in;
+  if (lane == 0) sh_last[wave] = wl;
+  __syncthreads();
+  double before = 0.0;
+  for (int w2 = 0; w2 < wave; ++w2) before += sh_w[w2];
+  const double cex = sh_cex, tgt = sh_tgt;
+  const double lo = cex + (before + ex), hi = cex + (before + in);
+  if (own > 0.0 && lo <= tgt && tgt < hi) {  // at most one thread: walk its run
+    double cum = lo;
+    int found = -1;
+    auto step = [&](int e, float m) {
+      if (found < 0 && m > 0.f) {
+        if (cum + (double)m > tgt) found = e;
+        cum += (double)m;
+      }
+    };
+    if (tid == 0)
+      for (int e = ch.hb; e < ch.he; ++e) step(e, em_h[e - ch.hb]);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+      if (has) step(eb + i, mm[i]);
+    if (tid == kLocThreads - 1)
+      for (int e = ch.tb; e < ch.te; ++e) step(e, em_t[e - ch.tb]);
     a.next_token[s] = found >= 0 ? found : elast;  // rounding: the run's last token with mass
     a.accept_len[s] = j;
     sh_hit = 1;

@@ -711,10 +711,11 @@ unsigned next_accept_tag() {
 constexpr int kMaxDevices = 64;  // devices whose per-device state the library keeps
 
 // Workgroups of a single-launch acceptance kernel the current device holds at once (the least
-// over the instantiations of accept_fused_kernel, kind 0, or accept_draw_kernel, kind 1), or 0
+// over the instantiations of accept_fused_kernel, kind 0, accept_draw_kernel, kind 1, or
+// accept_draw_multi_kernel, kind 2), or 0
 // if the runtime cannot tell; per device, computed on first use.
 int resident_capacity(int kind) {
-  static std::atomic<int> cap[2][kMaxDevices];
+  static std::atomic<int> cap[3][kMaxDevices];
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
     (void)hipGetLastError();
@@ -730,7 +731,8 @@ int resident_capacity(int kind) {
   const void *fused[] = {(const void *)sdb::accept_fused_kernel<true, true>, (const void *)sdb::accept_fused_kernel<true, false>,
                          (const void *)sdb::accept_fused_kernel<false, true>, (const void *)sdb::accept_fused_kernel<false, false>};
   const void *draw[] = {(const void *)sdb::accept_draw_kernel<true>, (const void *)sdb::accept_draw_kernel<false>};
-  const void *const *ks = kind == 0 ? fused : draw;
+  const void *multi[] = {(const void *)sdb::accept_draw_multi_kernel<true>, (const void *)sdb::accept_draw_multi_kernel<false>};
+  const void *const *ks = kind == 0 ? fused : kind == 1 ? draw : multi;
   const int nk = kind == 0 ? 4 : 2;
   int per_cu = INT_MAX;
   for (int i = 0; i < nk; ++i) {
@@ -827,19 +829,25 @@ int accept_enqueue(const sd_accept_shape *sh, const AcceptPlan &p, const void *t
   } while (0)
   // Sampling draw in one launch (mass and locate together) when the shape, the workspace, the
   // stream and the test switch allow it and the whole grid fits on the device at once with a
-  // quarter to spare (every workgroup of accept_draw_kernel waits for its sequence's others).
-  if (sample && p.draw_ok && workspace_bytes >= p.total_draw && g_accept_path.load(std::memory_order_relaxed) == 0 &&
-      4LL * S * p.nch2 <= 3LL * resident_capacity(1) && stream_allows_fused(st)) {
+  // quarter to spare (every workgroup of the draw kernels waits for its sequence's others): a chunk
+  // per workgroup where that fits, else kDrawChunks.
+  const bool draw_may = sample && p.draw_ok && workspace_bytes >= p.total_draw &&
+                        g_accept_path.load(std::memory_order_relaxed) == 0;
+  const long long grid_m = (long long)S * ((p.nch2 + sdb::kDrawChunks - 1) / sdb::kDrawChunks);
+  const int draw = !draw_may ? 0 : 4LL * S * p.nch2 <= 3LL * resident_capacity(1) ? 1 : 4 * grid_m <= 3LL * resident_capacity(2) ? 2 : 0;
+  if (draw && stream_allows_fused(st)) {
     a.csum = (unsigned long long *)(ws + p.off_draw);
     a.tag = next_accept_tag();
     const int spin = g_accept_spin.load(std::memory_order_relaxed);
     a.spin_limit = spin > 0 ? spin : kDefaultSpinLimit;
     if (bf) {
       SDB_STATS(true, true);
-      hipLaunchKernelGGL((sdb::accept_draw_kernel<true>), dim3(S * p.nch2), dim3(256), 0, st, a);
+      if (draw == 1) hipLaunchKernelGGL((sdb::accept_draw_kernel<true>), dim3(S * p.nch2), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((sdb::accept_draw_multi_kernel<true>), dim3((unsigned)grid_m), dim3(256), 0, st, a);
     } else {
       SDB_STATS(false, true);
-      hipLaunchKernelGGL((sdb::accept_draw_kernel<false>), dim3(S * p.nch2), dim3(256), 0, st, a);
+      if (draw == 1) hipLaunchKernelGGL((sdb::accept_draw_kernel<false>), dim3(S * p.nch2), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((sdb::accept_draw_multi_kernel<false>), dim3((unsigned)grid_m), dim3(256), 0, st, a);
     }
   } else if (sample) {
     if (bf) {

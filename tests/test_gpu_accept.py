@@ -237,7 +237,7 @@ _PATH_CASES = [
 _DRAW_CASES = [
     ("ragged", lambda: W.c3_ragged(temperatures=(1.0,), with_attn=False).accept[1.0]),
     ("qwen3_4b", lambda: W.c2_qwen3_4b_verify(temperatures=(1.0,)).accept[1.0]),
-    # 32 sequences x 75 chunks: more workgroups than the single launch takes (three launches)
+    # 32 sequences x 75 chunks: more workgroups than fit at once (four chunks per workgroup)
     ("long_context", lambda: W.c5_long_context(temperatures=(1.0,), with_attn=False).accept[1.0]),
     ("V4096_f32", lambda: _many_seq_problem(15, 40, 4096, (1, 20), "f32", 1.0, name="V4096_f32_T1")),
     # fp32 rows of 37984 vectors: 149 chunks, three passes of the chunk search
@@ -332,6 +332,39 @@ def test_single_launch_gives_up_when_told_and_recovers(T):
     else:
         assert ((al == alm) | (al == -1)).all() and ((nt == ntm) | (nt == -1)).all(), (al, alm, nt, ntm)
     al, nt = G.run_accept(p, d, workspace=ws)
+    assert (al == alm).all() and (nt == ntm).all()
+
+
+# More sampling chunks than a chunk per workgroup holds at once (S x chunks > 3/4 of the device's): four
+# chunks per workgroup, with a last group of one (25 chunks), three (35) or two (30) chunks, rows off the
+# vectors' alignment, and B_s = 1.
+_MULTI_CASES = [
+    ("V50001", lambda: _many_seq_problem(31, 60, 50001, (1, 5), "bf16", 1.0, target_sigma=3.0, noise_sigma=1.0,
+                                         name="multi_V50001")),
+    ("V70003", lambda: _many_seq_problem(32, 44, 70003, (1, 4), "bf16", 0.7, target_sigma=3.0, noise_sigma=1.0,
+                                         name="multi_V70003")),
+    ("V30001_f32", lambda: _many_seq_problem(33, 48, 30001, (1, 6), "f32", 1.0, target_sigma=3.0, noise_sigma=1.0,
+                                             name="multi_V30001_f32")),
+]
+
+
+@pytest.mark.parametrize("name,make", _MULTI_CASES, ids=[c[0] for c in _MULTI_CASES])
+def test_several_chunks_per_workgroup(name, make):
+    """The draw with several chunks per workgroup against the three launches, bit for bit, and the
+    oracle; with the waits cut to one poll every output is exact or -1, and the next call is exact."""
+    import paper_2606_31315_amd as sd
+    p = make()
+    d = G.accept_to_device(p)
+    (al1, nt1), (alm, ntm) = _both_paths(p, d)
+    assert (al1 == alm).all() and (nt1 == ntm).all(), (name, np.nonzero(al1 != alm), np.nonzero(nt1 != ntm))
+    G.compare_accept(p, al1, nt1, G.oracle_accept(p))
+    try:
+        sd.accept_set_path(0, 1)
+        al, nt = G.run_accept(p, d)
+    finally:
+        sd.accept_set_path(0)
+    assert ((al == alm) | (al == -1)).all() and ((nt == ntm) | (nt == -1)).all()
+    al, nt = G.run_accept(p, d)
     assert (al == alm).all() and (nt == ntm).all()
 
 
