@@ -56,9 +56,9 @@ struct AttnArgs {
   // fused append only: the block's new keys and values [total_q, Hkv, D]
   const void *k_new;
   const void *v_new;
-  // balanced plan (bf16, plain caches; bal_share): bal_grid workgroups, shares of at least
+  // balanced plan (bf16; bal_share): shares of at least
   // bal_min_tiles key tiles of bal_kt keys
-  int bal, bal_grid, bal_min_tiles, bal_kt;
+  int bal, bal_grid, bal_min_tiles, bal_kt;  // bal_grid: fp32, splits at most
   // fp32: m-tiles per workgroup at most (a block's m-tiles go to ceil(m-tiles / group_mt) workgroups,
   // evenly), the groups of the largest block, and the rows of a partial slot
   int group_mt, groups, part_rows;
@@ -225,9 +225,9 @@ __device__ __forceinline__ bool attn_item(const AttnArgs &a, int b, AttnItem &it
 
 // ---- balanced plan ---------------------------------------------------------------
 // Pair (s, g) holds n = ceil((ctx_s + B_s) / kt) key tiles (none when B_s = 0), each weighing
-// w = bal_weight(m-tiles of its block) units; the pairs line up in (sequence, kv head) order,
-// W units in all.  Workgroup w takes the tiles whose first unit lies in [w * per, (w + 1) * per),
-// per = max(ceil(W / bal_grid), bal_min_tiles * the lightest weight), so every workgroup gets
+// w = bal_weight(m-tiles of its block) units, after kBalPairCost units for its start; the pairs line
+// up in (sequence, kv head) order, W units in all.  Workgroup w takes the tiles whose first unit lies in [w * per, (w + 1) * per),
+// per = max(ceil(W / kBalGrid), bal_min_tiles * the lightest weight), so every workgroup gets
 // about the same work whatever the lengths are; its share is cut where it crosses from one pair
 // to the next, one work item per piece.  The piece of workgroup w in pair q = s * Hkv + g files
 // its partial at slot w + q, so a pair's pieces hold consecutive slots from (first workgroup) + q.
@@ -250,6 +250,17 @@ __device__ __forceinline__ int bal_weight(int nmt) {
   return nmt <= 8 ? kw[nmt] : kBalWeightMax8 + 4 * (nmt - 8);
 }
 
+constexpr int kBalGrid = 256;  // workgroups of the balanced plan: one per CU of the MI355X
+
+// Units a pair takes on the line ahead of its first tile: what starting it costs the workgroup
+// whose share runs on into it (the pair before filed, query rows and first tiles fetched), about five
+// tiles.  Less than the shortest share, so every workgroup between a pair's first and last holds
+// a tile of it.  us per call at 0 / 60 / 90 / 110 / 130 / 160 units: 16 sequences, contexts 1k-8k 64.8 / 62.0 / 61.1 /
+// 60.4 / 60.7 / 62.0; 32 sequences, contexts 8k-32k 451 / 450 / 443 / 445 / 443 / 444; 20 sequences, head_dim
+// 64, contexts 1k-12k 86.8 without, 79.5 / 79.6 / 79.4 at 90 / 110 / 130; 24 sequences, contexts 3k-16k
+// 144.1 without, 141.1 / 142.5 / 143.6.
+constexpr int kBalPairCost = 100;
+
 struct BalShare {
   int per, u0, u1;  // units per share; this workgroup's unit range [u0, u1)
 };
@@ -263,10 +274,13 @@ __device__ __forceinline__ int bal_seq_weight(const AttnArgs &a, int B) {
 }
 
 __device__ __forceinline__ int bal_per(const AttnArgs &a, int W) {
-  return max((W + a.bal_grid - 1) / a.bal_grid, a.bal_min_tiles * bal_weight(1));
+  return max((W + kBalGrid - 1) / kBalGrid, a.bal_min_tiles * bal_weight(1));
 }
 
-// First tile of a pair (start unit p0, weight w) whose first unit is at or after unit u.
+// Units of one pair of n tiles of weight w (0: no tiles, no pair).
+__device__ __forceinline__ int bal_pair_units(int n, int w) { return n > 0 ? n * w + kBalPairCost : 0; }
+
+// First tile of a pair (first tile's unit p0, weight w) whose first unit is at or after unit u.
 __device__ __forceinline__ int bal_tile_at(int u, int p0, int w) {
   return u <= p0 ? 0 : (u - p0 + w - 1) / w;
 }
@@ -278,7 +292,7 @@ __device__ __forceinline__ BalShare bal_share(const AttnArgs &a, int w, int kt) 
   for (int c0 = 0; c0 < a.S; c0 += 64) {
     const int k = min(c0 + lane, a.S - 1);  // clamped: no per-load branch
     const int B = a.block_lens[k];
-    const int u = bal_seq_tiles(c0 + lane < a.S, a.ctx_lens[k], B, kt) * bal_seq_weight(a, B) * a.Hkv;
+    const int u = bal_pair_units(bal_seq_tiles(c0 + lane < a.S, a.ctx_lens[k], B, kt), bal_seq_weight(a, B)) * a.Hkv;
     W += __builtin_amdgcn_readlane(wave_scan_i(u), 63);
   }
   BalShare sh;
@@ -306,19 +320,19 @@ __device__ __forceinline__ bool bal_item(const AttnArgs &a, BalShare &sh, int kt
       const int ctx = a.ctx_lens[k], B = a.block_lens[k], off = a.q_offsets[k];
       const int t = bal_seq_tiles(c0 + lane < a.S, ctx, B, kt);
       const int wt = bal_seq_weight(a, B);
-      const int sequ = t * wt * a.Hkv;
+      const int sequ = bal_pair_units(t, wt) * a.Hkv;
       const int incl = before + wave_scan_i(sequ);
       const unsigned long long hit = __ballot(incl > sh.u0 && incl - sequ <= sh.u0);  // holds unit u0
       if (hit) {
         const int l = __ffsll((long long)hit) - 1;  // wave-uniform
         const int ts = __builtin_amdgcn_readlane(t, l), w = __builtin_amdgcn_readlane(wt, l);
-        const int pu = ts * w;  // units of each of the sequence's pairs
+        const int pu = bal_pair_units(ts, w);  // units of each of the sequence's pairs
         const int pre = __builtin_amdgcn_readlane(incl - sequ, l);
         const int g = (sh.u0 - pre) / pu;
-        const int p0 = pre + g * pu;  // first unit of pair (s, g)
+        const int p0 = pre + g * pu + kBalPairCost;  // first tile's unit of pair (s, g)
         const int j0 = bal_tile_at(sh.u0, p0, w);
         if (j0 >= ts) {  // past the first unit of the pair's last tile: the next pair
-          sh.u0 = p0 + pu;
+          sh.u0 = p0 + ts * w;
           next_pair = true;
           break;
         }
@@ -335,7 +349,7 @@ __device__ __forceinline__ bool bal_item(const AttnArgs &a, BalShare &sh, int kt
         it.k0 = j0 * kt;
         it.k1 = min(j1 * kt, it.ctx + it.B);
         const int wf = p0 / sh.per, wl = (p0 + (ts - 1) * w) / sh.per;
-        const int wme = (p0 + j0 * w) / sh.per;  // this workgroup
+        const int wme = blockIdx.x;  // the piece's first unit lies in this workgroup's share
         it.nsplit = wl - wf + 1;
         it.split = wme - wf;
         it.slot = wme + it.s * a.Hkv + g;
@@ -358,7 +372,7 @@ __device__ __forceinline__ int2 attn_pair_slots(const AttnArgs &a, int s, int g,
       const int k = min(c0 + lane, a.S - 1);  // clamped: no per-load branch
       const int Bk = a.block_lens[k];
       const int t = bal_seq_tiles(c0 + lane < a.S, a.ctx_lens[k], Bk, a.bal_kt);
-      const int sequ = t * bal_seq_weight(a, Bk) * a.Hkv;
+      const int sequ = bal_pair_units(t, bal_seq_weight(a, Bk)) * a.Hkv;
       const int incl = wave_scan_i(sequ);
       if (s >= c0 && s < c0 + 64) {  // wave-uniform
         const int l = s - c0;
@@ -371,7 +385,7 @@ __device__ __forceinline__ int2 attn_pair_slots(const AttnArgs &a, int s, int g,
     B = Bs;
     if (Bs <= 0) return int2{0, 0};
     const int per = bal_per(a, W), w = bal_seq_weight(a, Bs);
-    const int p0 = pre + g * ts * w;
+    const int p0 = pre + g * bal_pair_units(ts, w) + kBalPairCost;
     const int wf = p0 / per, wl = (p0 + (ts - 1) * w) / per;
     return int2{wf + s * a.Hkv + g, wl - wf + 1};
   }

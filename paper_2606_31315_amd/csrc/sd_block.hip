@@ -78,9 +78,9 @@ struct AttnPlan {
   size_t off_ml, off_o, total;
 };
 
-// Balanced plan: one workgroup per CU of the MI355X (the bf16 split kernel holds a CU), each
+// Balanced plan: one workgroup per CU (the bf16 split kernel holds a CU), each
 // share at least 16 key tiles (1024 keys), like the shortest split of the other multi-wave plans.
-constexpr int kBalGrid = 256;
+using sdb::kBalGrid;
 constexpr int kBalMinTiles = 16;
 #ifndef SDB_F32_MIN_TILES
 #define SDB_F32_MIN_TILES 2
@@ -173,7 +173,7 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   {  // the device sums tile weights (at most kBalWeightMax8 + 4 per m-tile past 8) in 32-bit integers
     const long long nmt_max = (G * (long long)sh->max_block + 15) / 16;
     const long long wmax = sdb::kBalWeightMax8 + 4 * std::max(0LL, nmt_max - 8);
-    if (pairs * ((max_L + kBf16KT - 1) / kBf16KT) * wmax > (1LL << 30)) p->bal = 0;
+    if (pairs * ((max_L + kBf16KT - 1) / kBf16KT * wmax + sdb::kBalPairCost) > (1LL << 30)) p->bal = 0;
   }
   const long long slots = p->bal ? std::max(nw, (long long)kBalGrid + pairs) : nw;
   const int nmt = p->Mpad / 16;
@@ -221,16 +221,23 @@ void launch_attn_bal(sdb::AttnArgs a, int MT, hipStream_t st, bool ve) {
   a.bal = 1;
   if (ve)
     hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND, true, true>),
-                       dim3(a.bal_grid), dim3(512), 0, st, a);
+                       dim3(kBalGrid), dim3(512), 0, st, a);
   else if (MT == 1)
-    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND, true>), dim3(a.bal_grid),
+    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 1, kBf16KT, kBf16NS, PAGED, APPEND, true>), dim3(kBalGrid),
                        dim3(512), 0, st, a);
   else
-    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 2, kBf16KT, kBf16NS, PAGED, APPEND, true>), dim3(a.bal_grid),
+    hipLaunchKernelGGL((sdb::block_attn_bf16_kernel<D, 2, kBf16KT, kBf16NS, PAGED, APPEND, true>), dim3(kBalGrid),
                        dim3(512), 0, st, a);
   constexpr int RB = 256 / (D / 4);
   const int nrb = (a.Mpad + RB - 1) / RB;
-  hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 8>), dim3(a.S * a.Hkv * nrb), dim3(256), 0, st, a);
+  const dim3 g(a.S * a.Hkv * nrb);
+  // splits of a pair read in one round: a pair touches about kBalGrid / pairs + 1 shares, and reading
+  // past them costs more than a second round does (16 sequences, contexts 1k-8k, 128 pairs: 65.5 us per
+  // call with 8, 64.1 with 4, 64.3 with 3; 32 sequences, contexts 8k-32k, 256 pairs: 455.6, 451.9, 448.0)
+  const int pairs = a.S * a.Hkv;
+  if (pairs >= kBalGrid / 2) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 3>), g, dim3(256), 0, st, a);
+  else if (pairs >= kBalGrid / 4) hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 4>), g, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((sdb::block_attn_merge_kernel<true, D, 8>), g, dim3(256), 0, st, a);
 }
 
 template <int D, bool PAGED = false, bool APPEND = false>
