@@ -140,12 +140,13 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _cur_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream):
+    """The stream's handle for a c_void_p argument."""
     if stream is None:
         if _raw_stream is not None and _cur_device is not None:
-            return ctypes.c_void_p(_raw_stream(_cur_device()))
+            return _raw_stream(_cur_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -193,6 +194,14 @@ def _need(t: torch.Tensor, name: str, dtype=None, device=None):
         raise ValueError(f"{name} is on {t.device}, expected {device}")
 
 
+def _ok(t, dev: int, dtype, shape) -> bool:
+    """True for a plain tensor that passes every check of _shape and _need as it stands: the per-step
+    calls ask this first (a few attribute reads) and go through the full checks, which name what is
+    wrong, only where it fails."""
+    return (type(t) is torch.Tensor and t.get_device() == dev and t.dtype is dtype and t.shape == shape
+            and t.is_contiguous())
+
+
 class Workspace:
     """A device scratch buffer per device, grown on demand; calls sharing it must be
     ordered (one stream)."""
@@ -220,20 +229,22 @@ def attn_shape(q: torch.Tensor, k_cache: torch.Tensor, max_ctx: int, max_block: 
                        float(scale))
 
 
-# Shape structs of the per-step calls, by their field values: the library only reads them, so
-# one struct serves every call of that shape (building one costs about a microsecond of host
-# time).  Bounded: cleared when it grows past _SHAPE_CACHE_MAX entries.
-_SHAPE_CACHE_MAX = 256
-_shape_cache: dict = {}
+# What a per-step call needs besides its tensors, by the values that decide it: the shape struct (the
+# library only reads it, so one serves every call of that shape), a reference to it, and the workspace
+# bytes (a function of the shape).  Building and asking for them costs a few microseconds of host time.
+# Bounded: cleared when it grows past _CALL_CACHE_MAX entries.
+_CALL_CACHE_MAX = 256
+_call_cache: dict = {}
 
 
-def _cached_shape(key, make):
-    sh = _shape_cache.get(key)
-    if sh is None:
-        if len(_shape_cache) >= _SHAPE_CACHE_MAX:
-            _shape_cache.clear()
-        sh = _shape_cache[key] = make()
-    return sh
+def _cached_call(key, make_shape, nbytes):
+    c = _call_cache.get(key)
+    if c is None:
+        if len(_call_cache) >= _CALL_CACHE_MAX:
+            _call_cache.clear()
+        shape = make_shape()
+        c = _call_cache[key] = (shape, ctypes.byref(shape), nbytes(shape))
+    return c
 
 
 def attn_workspace_size(shape: SdAttnShape) -> int:
@@ -249,6 +260,35 @@ def block_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, ct
     """Block attention (sd_block_attn).  q [total_q, Hq, D]; caches [S, Hkv, Lmax, D];
     ctx_lens, block_lens [S] and q_offsets [S+1] int32 on the device; max_ctx and
     max_block are host-known bounds of the device lengths."""
+    if not _block_attn_ok(q, k_cache, v_cache, ctx_lens, block_lens, q_offsets, out):
+        _block_attn_checks(q, k_cache, v_cache, ctx_lens, block_lens, q_offsets, out)
+    S, Hkv, Lmax, D = k_cache.shape
+    total_q, Hq, _ = q.shape
+    if out is None:
+        out = torch.empty_like(q)
+    shape, ref, nbytes = _cached_call(("attn", S, Hq, Hkv, D, Lmax, total_q, int(max_ctx), int(max_block), q.dtype,
+                                       float(scale)),
+                                      lambda: attn_shape(q, k_cache, max_ctx, max_block, scale), attn_workspace_size)
+    if workspace is None:  # a caller's workspace is checked against the need by the library
+        workspace = _default_ws.get(nbytes, q.device)
+    _check(lib().sd_block_attn(ref, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), ctx_lens.data_ptr(),
+                               block_lens.data_ptr(), q_offsets.data_ptr(), int(mask_mode), out.data_ptr(),
+                               workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream(stream)))
+    return out
+
+
+def _block_attn_ok(q, k_cache, v_cache, ctx_lens, block_lens, q_offsets, out) -> bool:
+    if type(q) is not torch.Tensor or type(k_cache) is not torch.Tensor or q.dim() != 3 or k_cache.dim() != 4:
+        return False
+    dev, dt, ks = q.get_device(), q.dtype, k_cache.shape
+    S = ks[0]
+    return (dev >= 0 and q.is_contiguous() and q.shape[2] == ks[3] and _ok(k_cache, dev, dt, ks)
+            and _ok(v_cache, dev, dt, ks) and _ok(ctx_lens, dev, torch.int32, (S,))
+            and _ok(block_lens, dev, torch.int32, (S,)) and _ok(q_offsets, dev, torch.int32, (S + 1,))
+            and (out is None or _ok(out, dev, dt, q.shape)))
+
+
+def _block_attn_checks(q, k_cache, v_cache, ctx_lens, block_lens, q_offsets, out) -> None:
     _shape(k_cache, "k_cache", None, None, None, None)
     S, Hkv, Lmax, D = k_cache.shape
     _shape(q, "q", None, None, D)
@@ -262,17 +302,8 @@ def block_attn(q: torch.Tensor, k_cache: torch.Tensor, v_cache: torch.Tensor, ct
     _need(v_cache, "v_cache", q.dtype, dev)
     for name, t in (("ctx_lens", ctx_lens), ("block_lens", block_lens), ("q_offsets", q_offsets)):
         _need(t, name, torch.int32, dev)
-    if out is None:
-        out = torch.empty_like(q)
-    _need(out, "out", q.dtype, dev)
-    shape = _cached_shape(("attn", S, q.shape[1], Hkv, D, Lmax, q.shape[0], int(max_ctx), int(max_block), q.dtype,
-                           float(scale)), lambda: attn_shape(q, k_cache, max_ctx, max_block, scale))
-    if workspace is None:  # a caller's workspace is checked against the need by the library
-        workspace = _default_ws.get(attn_workspace_size(shape), dev)
-    _check(lib().sd_block_attn(ctypes.byref(shape), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(ctx_lens),
-                               _ptr(block_lens), _ptr(q_offsets), int(mask_mode), _ptr(out), _ptr(workspace),
-                               workspace.numel() * workspace.element_size(), _stream(stream)))
-    return out
+    if out is not None:
+        _need(out, "out", q.dtype, dev)
 
 
 def block_attn_append(q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, k_cache: torch.Tensor,
@@ -423,23 +454,44 @@ def accept(target_logits: torch.Tensor, draft_logits: Optional[torch.Tensor], dr
            *, max_block: int, accept_len: Optional[torch.Tensor] = None, next_token: Optional[torch.Tensor] = None,
            workspace: Optional[torch.Tensor] = None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Speculative acceptance (sd_accept).  Returns device int32 (accept_len[S], next_token[S])."""
-    S = _accept_checks(target_logits, draft_logits, draft_tokens, uniforms, block_lens, q_offsets, temperature,
+    sample = temperature > 0
+    if not _accept_ok(target_logits, draft_logits, draft_tokens, uniforms, block_lens, q_offsets, sample, accept_len,
+                      next_token):
+        _accept_checks(target_logits, draft_logits, draft_tokens, uniforms, block_lens, q_offsets, temperature,
                        accept_len, next_token)
+    S = block_lens.shape[0]
+    total_q, V = target_logits.shape
     dev = target_logits.device
     if accept_len is None:
         accept_len = torch.empty(S, dtype=torch.int32, device=dev)
     if next_token is None:
         next_token = torch.empty(S, dtype=torch.int32, device=dev)
-    shape = _cached_shape(("accept", S, target_logits.shape[1], target_logits.shape[0], int(max_block),
-                           target_logits.dtype), lambda: accept_shape(target_logits, S, max_block))
+    temperature = float(temperature)
+    shape, ref, nbytes = _cached_call(("accept", S, V, total_q, int(max_block), target_logits.dtype, temperature),
+                                      lambda: accept_shape(target_logits, S, max_block),
+                                      lambda sh: accept_workspace_size(sh, temperature))
     if workspace is None:  # a caller's workspace is checked against the need by the library
-        workspace = _default_ws.get(accept_workspace_size(shape, temperature), dev)
-    _check(lib().sd_accept(ctypes.byref(shape), _ptr(target_logits),
-                           _ptr(draft_logits if temperature > 0 else None), _ptr(draft_tokens),
-                           _ptr(uniforms if temperature > 0 else None), _ptr(block_lens), _ptr(q_offsets),
-                           float(temperature), _ptr(accept_len), _ptr(next_token), _ptr(workspace),
+        workspace = _default_ws.get(nbytes, dev)
+    _check(lib().sd_accept(ref, target_logits.data_ptr(), _ptr(draft_logits if sample else None), _ptr(draft_tokens),
+                           _ptr(uniforms if sample else None), block_lens.data_ptr(), q_offsets.data_ptr(),
+                           temperature, accept_len.data_ptr(), next_token.data_ptr(), workspace.data_ptr(),
                            workspace.numel() * workspace.element_size(), _stream(stream)))
     return accept_len, next_token
+
+
+def _accept_ok(target_logits, draft_logits, draft_tokens, uniforms, block_lens, q_offsets, sample, accept_len,
+               next_token) -> bool:
+    if (type(target_logits) is not torch.Tensor or type(block_lens) is not torch.Tensor or target_logits.dim() != 2
+            or block_lens.dim() != 1):
+        return False
+    dev, dt, (total_q, V), S, i32 = (target_logits.get_device(), target_logits.dtype, target_logits.shape,
+                                     block_lens.shape[0], torch.int32)
+    return (dev >= 0 and target_logits.is_contiguous() and _ok(block_lens, dev, i32, (S,))
+            and _ok(q_offsets, dev, i32, (S + 1,)) and _ok(draft_tokens, dev, i32, (total_q - S,))
+            and (not sample or (_ok(draft_logits, dev, dt, (total_q - S, V))
+                                and _ok(uniforms, dev, torch.float32, (total_q,))))
+            and (accept_len is None or _ok(accept_len, dev, i32, (S,)))
+            and (next_token is None or _ok(next_token, dev, i32, (S,))))
 
 
 def accept_noalloc(target_logits: torch.Tensor, draft_logits: Optional[torch.Tensor], draft_tokens: torch.Tensor,

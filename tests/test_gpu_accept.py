@@ -400,3 +400,24 @@ def test_small_workspace_takes_multi_launch_path(T):
     torch.cuda.synchronize()
     _, multi = _both_paths(p, d)
     assert (al.cpu().numpy() == multi[0]).all() and (nt.cpu().numpy() == multi[1]).all()
+
+
+def test_binding_still_names_what_is_wrong_on_the_device():
+    """Device tensors that fail a check of the per-step calls' quick test get the full checks' error, and
+    forms that only those accept (more drafted tokens than rows) still run."""
+    import paper_2606_31315_amd as sd
+    p = _many_seq_problem(41, 3, 1003, (2, 6), "f32", 1.0, name="binding")
+    d = G.accept_to_device(p)
+    args = [d["t"], d["d"], d["tok"], d["u"], d["bl"], d["off"]]
+    al, nt = sd.accept(*args, 1.0, max_block=p.max_block)
+    longer = list(args)
+    longer[2] = torch.cat([args[2], torch.zeros(5, dtype=torch.int32, device=G.dev())])
+    al2, nt2 = sd.accept(*longer, 1.0, max_block=p.max_block)
+    assert torch.equal(al, al2) and torch.equal(nt, nt2)
+    for i, bad, err in [(0, args[0].t().contiguous().t(), ValueError), (1, args[1][:-1], ValueError),
+                        (2, args[2].long(), TypeError), (3, args[3].double(), TypeError), (4, args[4].cpu(), ValueError),
+                        (5, args[5][:-1], ValueError), (1, args[1].bfloat16(), TypeError)]:
+        a = list(args)
+        a[i] = bad
+        with pytest.raises(err):
+            sd.accept(*a, 1.0, max_block=p.max_block)
