@@ -5,24 +5,15 @@
 // bidirectionally for the block-diffusion drafter.  Query head h reads kv head
 // h / G with G = Hq / Hkv.
 //
-// Kernel design (gfx950):
-//   * One workgroup (4 wavefronts) per (sequence, kv head, KV split).  All G*B_s
-//     query rows of the sequence's kv-head group are packed into 16-row MFMA tiles,
-//     so each K/V byte is read from HBM once for the whole group.
-//   * K tile staged in LDS row-major; V tile written to LDS transposed
-//     (d-major, 4 consecutive keys per 8-byte word) so the P.V contraction over keys
-//     reads its operand with 8-byte LDS loads.
-//   * S^T = K Q^T on v_mfma_f32_16x16x32_bf16 (16x16x4_f32 for fp32 inputs): each lane
-//     then owns four keys of one query row, which is exactly the B-operand layout the
-//     O^T += V^T P^T MFMA needs, so P never leaves registers.
-//   * Online softmax in the log2 domain (scale * log2 e folded into one FMA), with
-//     per-lane partial row sums reduced once at the end.
-//   * A sequence whose keys fit one split writes its output directly.  Otherwise each
-//     split writes fp32 partials (unnormalised O, row max, row sum) and a second launch,
-//     block_attn_merge_kernel, combines them.  The kernel boundary is the only
-//     cross-workgroup synchronisation: an in-kernel "last workgroup merges" scheme needs
-//     agent-scope release fences, which on gfx950 write back the XCD's L2 and cost far
-//     more than the second launch.
+// This file holds what the split kernels (attn_bf16.hpp, attn_f32.hpp) share: the kernel arguments,
+// the plans that cut the keys of every (sequence, kv head) pair into work items on the device, and the
+// merge.  All G*B_s query rows of a sequence's kv-head group are packed into 16-row MFMA tiles
+// (m-tiles), so each K/V byte is read from HBM once for the whole group.  A pair whose keys fit one
+// split writes its output directly.  Otherwise each split writes fp32 partials (unnormalised O, row
+// max in log2 units, row sum) and a second launch, block_attn_merge_kernel, combines them.  The kernel
+// boundary is the only cross-workgroup synchronisation: an in-kernel "last workgroup merges" scheme
+// needs agent-scope release fences, which on gfx950 write back the XCD's L2 and cost far
+// more than the second launch.
 #pragma once
 
 #include "common.hpp"

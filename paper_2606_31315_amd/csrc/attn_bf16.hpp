@@ -1,9 +1,8 @@
 // attn_bf16.hpp -- bf16 block attention kernel built around gfx950's asynchronous
 // global-to-LDS loads.
 //
-// Same operation and work decomposition as block_attn_kernel (one workgroup per
-// (sequence, kv head, KV split); all G*B_s query rows of the kv-head group packed into
-// 16-row MFMA tiles), with the memory pipeline rebuilt for bandwidth:
+// One workgroup per (sequence, kv head, KV split), or per share of the balanced plan; all G*B_s query
+// rows of the kv-head group packed into 16-row MFMA tiles:
 //   * 8 wavefronts; wavefront w owns m-tiles w, w+8 (so up to 128 query rows per
 //     m-tile slot).
 //   * K and V tiles (64 keys each) are fetched with global_load_lds_dwordx4 straight

@@ -50,9 +50,6 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Butterfly reductions inside a wavefront over lanes that differ in the given xor mask bits.
-__device__ __forceinline__ float shfl_xor_f(float v, int mask) { return __shfl_xor(v, mask, kWave); }
-
 // Wait until at most N of this wavefront's vector memory operations are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -71,11 +68,6 @@ __device__ __forceinline__ T ld_uniform(const T *p, long long i) {
 __device__ __forceinline__ float4 ld_uniform4(const float4 *p, long long i) {
   const float *f = reinterpret_cast<const float *>(p) + 4 * i;
   return float4{ld_uniform(f, 0), ld_uniform(f, 1), ld_uniform(f, 2), ld_uniform(f, 3)};
-}
-
-// Opaque to the optimiser: values derived from v before this point are not reused after it.
-__device__ __forceinline__ void reg_barrier(u32x4 &v) {
-  asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
 }
 
 // ---- wavefront reductions and scans through DPP lane moves (no LDS round trips) ----
