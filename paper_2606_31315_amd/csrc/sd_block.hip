@@ -1239,6 +1239,7 @@ int sd_survival_tau(const sd_survival_shape *sh, const float *gamma, const int32
   a.b_star = b_star;
   a.regret = regret;
   a.lipschitz = lipschitz;
+  a.load_nt = sdb::tau_load_nt(a.N, a.P, a.C);
   const int grid = (int)(((long long)a.N + 63) / 64);
   hipLaunchKernelGGL(sdb::survival_tau_kernel, dim3(grid), dim3(64), sdb::tau_lds(a.P, a.C), (hipStream_t)stream, a);
   return check_launch("sd_survival_tau");

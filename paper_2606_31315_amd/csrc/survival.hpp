@@ -40,6 +40,7 @@ struct SurvivalArgs {
   int *len_hist;        // [N, C, P + 1] or null (sampler)
   unsigned long long seed;
   int N, P, C, train_block, trials;
+  int load_nt;          // tau: gamma is read past the caches
   double alpha;
   int cands[kSurvMaxCands];
 };
@@ -50,7 +51,7 @@ __device__ __forceinline__ double retention(int b, int B, double alpha) {
 }
 
 // One wavefront per workgroup, one sample per lane: no barrier joins one wavefront's loads to
-// another's arithmetic, and the LDS of a CU holds 18 of them at 32 positions.  The samples' gamma rows
+// another's arithmetic, and the registers hold 16 of them on a CU.  The samples' gamma rows
 // are one contiguous run, read as 16-byte vectors (every load of 8 KB in flight at once) into LDS rows of
 // odd stride, so that the lanes' row reads fall in distinct banks.  Up to kTauCands candidates
 // are carried through one pass over the row, as many independent chains of products as there are;
@@ -60,13 +61,29 @@ __device__ __forceinline__ double retention(int b, int B, double alpha) {
 // 46.1 us with every position tested against each candidate's size past the first, 42.5 with a
 // division only where candidates are not neighbours and non-temporal accesses, 39.6 with the positions
 // between two sizes run for the remaining candidates alone.
+// Up to kTauStaged candidates are staged and stored together: a pass's part of a row is stored past the
+// caches in pieces of lines otherwise (2^19 samples x 32 positions, 9 / 11 candidates: pass by pass 41.4 /
+// 52.0 us, together 32.5 / 36.2; the 256-thread kernel 42.4 / 51.3).  Beyond, the passes are stored
+// through the caches unless their parts are whole 64-byte runs (17 candidates 85.4 / 57.2 us; 24 candidates
+// x 2^18 x 64 positions 52.9 past the caches, 54.4 through them).
 constexpr int kTauCands = 8;
+constexpr int kTauStaged = 16;
 
-// Dynamic LDS: the gamma rows, and the tau of a pass (where one pass takes every candidate, in
+// Whether gamma is read past the caches: not where a user's next call may find it in the 256 MB Infinity
+// Cache and there are so few candidates that the read is most of the time.  us from memory / from the
+// cache, past the caches and through them: 2^20 x 20 positions x 3 candidates 29.3 / 28.8 and 30.5 / 25.5 (the
+// 256-thread kernel 31.6 / 26.9), 2^20 x 32 x 3 35.3 / 35.3 and 37.5 / 35.9 (40.9 / 39.5), 2^19 x 32 x 5
+// 22.5 / 21.8 and 24.0 / 20.5 (28.6 / 25.0).
+__host__ inline bool tau_load_nt(int N, int P, int C) { return C > 3 || 4LL * N * P >= (1LL << 27); }
+
+// Candidates whose tau are staged together: all of them up to kTauStaged, else those of a pass.
+__host__ __device__ inline int tau_staged(int C) { return C <= kTauStaged ? C : kTauCands; }
+
+// Dynamic LDS: the gamma rows, and the staged tau (where one pass takes every candidate, in
 // their place).
 __host__ __device__ inline int tau_rows_bytes(int P) { return 64 * ((P + 1) | 1) * (int)sizeof(float); }
 __host__ __device__ inline int tau_lds(int P, int C) {
-  const int rows = (tau_rows_bytes(P) + 15) & ~15, out = 64 * (C < kTauCands ? C : kTauCands) * (int)sizeof(double);
+  const int rows = (tau_rows_bytes(P) + 15) & ~15, out = 64 * tau_staged(C) * (int)sizeof(double);
   return C <= kTauCands ? (rows > out ? rows : out) : rows + out;
 }
 
@@ -150,30 +167,35 @@ __global__ __launch_bounds__(64) void survival_tau_kernel(SurvivalArgs a) {
   const long long n0 = (long long)blockIdx.x * 64;
   const int rows = (int)min(64LL, (long long)a.N - n0);
   const int bh = (a.b_hat && lane < rows) ? a.b_hat[n0 + lane] : -1;
-  // the rows are one contiguous run of rows * P floats; 16-byte loads when P % 4 == 0
+  // the rows are one contiguous run of rows * P floats from a multiple of 64 P on, so 16-byte aligned
+  // whatever P is; element 4 v of the run is (row, col), and 64 vectors on dr rows and dc columns further
   const float *src = a.gamma + n0 * P;
-  const int total = rows * P;
-  if ((P & 3) == 0) {
+  const int total = rows * P, nvec = total / 4;
+  const int dr = 256 / P, dc = 256 - dr * P;
+  int row = (4 * lane) / P, col = 4 * lane - row * P;
+  auto stage = [&](auto whole_c, auto nt_c) {  // whole_c: P % 4 == 0, a vector's floats share a row
+    constexpr bool WHOLE = decltype(whole_c)::value, NT = decltype(nt_c)::value;
     const f32x4 *s4 = reinterpret_cast<const f32x4 *>(src);
-    const int nvec = total / 4;
-    // element 4 v of the run is (row, col); 64 vectors on, it moves by dr rows and dc columns
-    const int dr = 256 / P, dc = 256 - dr * P;
-    int row = (4 * lane) / P, col = 4 * lane - row * P;
     for (int v0 = lane; v0 < nvec; v0 += 8 * 64) {
       f32x4 x[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {  // clamped: no per-load branch
         const f32x4 *p = s4 + min(v0 + k * 64, nvec - 1);
-        x[k] = __builtin_nontemporal_load(p);
+        x[k] = NT ? __builtin_nontemporal_load(p) : *p;
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         if (v0 + k * 64 < nvec) {
-          float *d = lds + row * stride + col;  // P % 4 == 0: the 4 floats share a row
-          d[0] = x[k][0];
-          d[1] = x[k][1];
-          d[2] = x[k][2];
-          d[3] = x[k][3];
+          int r = row, c = col;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lds[r * stride + c] = x[k][e];
+            ++c;
+            if (!WHOLE && c == P) {
+              c = 0;
+              ++r;
+            }
+          }
         }
         row += dr;
         col += dc;
@@ -183,8 +205,17 @@ __global__ __launch_bounds__(64) void survival_tau_kernel(SurvivalArgs a) {
         }
       }
     }
+  };
+  using std::false_type;
+  using std::true_type;
+  if ((P & 3) == 0) {
+    if (a.load_nt) stage(true_type{}, true_type{});
+    else stage(true_type{}, false_type{});
   } else {
-    for (int e = lane; e < total; e += 64) lds[(e / P) * stride + e % P] = src[e];
+    if (a.load_nt) stage(false_type{}, true_type{});
+    else stage(false_type{}, false_type{});
+    const int e = 4 * nvec + lane;
+    if (e < total) lds[(e / P) * stride + e % P] = src[e];
   }
   const double r_lane = retention(a.cands[min(lane, C - 1)], a.train_block, a.alpha);
   __syncthreads();
@@ -204,13 +235,20 @@ __global__ __launch_bounds__(64) void survival_tau_kernel(SurvivalArgs a) {
       default: tau_pass<8>(a, g, c0, r_lane, bh, st, t); break;
     }
     __syncthreads();  // the rows are read (their place is reused where this is the only pass)
+    const bool all = C <= kTauStaged;
+    const int ow = all ? C : nc, oc = all ? c0 : 0;  // the staged row's width, this pass's place in it
 #pragma unroll
     for (int c = 0; c < kTauCands; ++c)
-      if (c < nc) out[lane * nc + c] = t[c];
+      if (c < nc) out[lane * ow + oc + c] = t[c];
+    if (all && c0 + nc < C) continue;
     __syncthreads();
-    for (int f = lane; f < rows * nc; f += 64) {
-      const long long o = C <= kTauCands ? n0 * C + f : (n0 + f / nc) * C + c0 + f % nc;
-      __builtin_nontemporal_store(out[f], a.tau + o);
+    if (all) {
+      for (int f = lane; f < rows * C; f += 64) __builtin_nontemporal_store(out[f], a.tau + n0 * C + f);
+    } else if ((C & 7) == 0) {  // whole 64-byte runs
+      for (int f = lane; f < rows * kTauCands; f += 64)
+        __builtin_nontemporal_store(out[f], a.tau + (n0 + f / kTauCands) * C + c0 + f % kTauCands);
+    } else {
+      for (int f = lane; f < rows * nc; f += 64) a.tau[(n0 + f / nc) * C + c0 + f % nc] = out[f];
     }
     __syncthreads();  // before the next pass writes out
   }

@@ -68,10 +68,13 @@ def test_tau_64_candidates_128_positions():
 
 @pytest.mark.parametrize("N,P,cands", [(1, 1, [1]), (63, 7, [1, 7]), (64, 16, [3, 4, 9]), (65, 33, [4, 8, 12, 33]),
                                        (130, 32, [1, 2, 3, 5, 8, 13, 21, 32]), (67, 40, [2, 6, 7, 11, 15, 16, 18, 30, 40]),
-                                       (66, 128, list(range(8, 129, 8)))])
+                                       (66, 128, list(range(8, 129, 8))), (129, 13, list(range(2, 12))),
+                                       (65, 3, [1, 2, 3]), (3, 2, [1]), (191, 22, list(range(4, 21))),
+                                       (70, 37, list(range(8, 32))), (64, 128, list(range(1, 17)))])
 def test_tau_candidate_passes(N, P, cands):
-    """One candidate to two full passes of eight, neighbours and gaps of every length mod 4, positions a
-    multiple of four or not, and samples on both sides of a wavefront."""
+    """One candidate to three full passes of eight, staged together (up to 16) or pass by pass (17 and 24),
+    neighbours and gaps of every length mod 4, positions a multiple of four or not (rows shorter than a
+    vector, a run whose last vector is partial), and samples on both sides of a wavefront."""
     p = W.make_survival(37, N=N, P=P, train_block=max(1, P // 2), radius=0, alpha=0.003)
     p.cands = np.array(cands, dtype=np.int32)
     p.b_hat = p.cands[np.arange(N) % len(cands)].astype(np.int32)
