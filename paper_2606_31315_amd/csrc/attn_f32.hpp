@@ -24,6 +24,16 @@
 // blocks of 12 233 -> 140; 32 sequences, contexts 2048, blocks of 16 241 -> 171.  Of the 28.8 us of the
 // first one's split kernel the plan takes 1.9, the query rows 3.5, the first tile 2.4, four or five tiles 3.2
 // each, the merge of the states 2.
+//   * Where whole pairs are the better cut (few keys, or more groups than CUs and contexts that are not
+//     long; AttnPlan::whole) the same kernel runs with two key slots: 8 wavefronts and 67 KB of LDS, so that
+//     a CU holds two of them, and no merge launch.  us per call, register-staged kernel / splits / whole
+//     pairs, G = 4 and head_dim 128 unless named: 99 sequences x 8 kv heads, contexts 0-5, blocks of 11
+//     21.6 / 38.6 / 20.3; 91 x 4, G = 1, contexts 0-1, blocks of 12-26 10.5 / 15.8 / 7.7; 100 x 8, contexts
+//     120-184, blocks of 8 87.9 / 73.5 / 43.1; 224 x 8, G = 2, head_dim 64, the same contexts 84.4 / 85.5 / 38.3.
+//     Geometric means over random shapes, splits and whole pairs, of the time over the register-staged
+//     kernel's: up to 32 keys 1.14-1.6 and 0.77-0.95; up to 256 groups, 100-192 keys 0.49-0.63 and 0.50-0.58, 384
+//     keys 0.53 and 0.58-0.69; more groups, 64-192 keys 0.62-1.24 and 0.49-0.66, 384-1024 keys 0.49-0.69 and 0.40-0.57
+//     (these before a workgroup found its pair without a look at the others: f32_whole_item).
 #pragma once
 
 #include "attn.hpp"
@@ -33,15 +43,18 @@ namespace sdb {
 constexpr int kF32Waves = 16;
 constexpr int kF32GroupMT = 4;  // m-tiles per work item at most
 
-template <int D>
+// NK key slots of 16 keys: a wavefront for each slot and m-tile.
+template <int D, int NK>
 struct F32Tile {
+  static constexpr int NW = NK * kF32GroupMT;     // wavefronts
   static constexpr int ROWB = D * 4;              // bytes per key row
   static constexpr int CPR = ROWB / 16;           // 16-byte vectors per row
-  static constexpr int TILEB = kF32KT * ROWB;     // bytes of a K (or V) tile
+  static constexpr int TILEB = 16 * NK * ROWB;    // bytes of a K (or V) tile
   static constexpr int RPI = 1024 / ROWB;         // rows written by one 1 KB transfer
   static constexpr int LPI = TILEB / 1024;        // transfers per K (or V) tile
-  static constexpr int LPW = 2 * LPI / kF32Waves;  // transfers per wavefront and tile
+  static constexpr int LPW = 2 * LPI / NW;        // transfers per wavefront and tile
   static constexpr int STAGEB = 2 * TILEB;        // K tile then V tile; two stages
+  static constexpr int QB = 16 * kF32GroupMT * ROWB;  // bytes of the query rows
 };
 
 // K operands of a 16-key tile: k[t] dims 16 t + 4 kgrp .. +3 of key l16.  V operands: v[r][h] dims
@@ -141,20 +154,41 @@ __device__ __forceinline__ bool f32_item(const AttnArgs &a, int b, F32Item &it) 
   return false;  // past the last item
 }
 
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs a) {
-  using T = F32Tile<D>;
+// Whole pairs: workgroup b of S x Hkv x a.groups, without a look at the other sequences.
+__device__ __forceinline__ bool f32_whole_item(const AttnArgs &a, int b, F32Item &it) {
+  const int pair = b / a.groups;
+  it.grp = b - pair * a.groups;
+  it.s = pair / a.Hkv;
+  it.g = pair - it.s * a.Hkv;
+  it.ctx = ld_uniform(a.ctx_lens, it.s);
+  it.B = ld_uniform(a.block_lens, it.s);
+  it.qoff = ld_uniform(a.q_offsets, it.s);
+  const int2 gr = f32_groups(a, it.B);
+  it.gmt = gr.y;
+  it.split = it.slot = 0;
+  it.nsplit = 1;
+  return it.B > 0 && it.grp < gr.x;
+}
+
+// NK = 4: f32_item's splits; NK = 2: whole pairs (a.bal = 0).
+template <int D, int NK>
+__global__ __launch_bounds__(64 * NK * kF32GroupMT, 4) void block_attn_f32_kernel(AttnArgs a) {
+  using T = F32Tile<D, NK>;
   constexpr int NT4 = D / 16, NH = D / 64, NO = NH * 16;  // NO: output floats per lane
-  static_assert(kF32Waves * NO * 256 <= 2 * T::STAGEB, "the states are exchanged through the ring");
+  constexpr int KT = 16 * NK;
+  constexpr bool PLAN = NK == 4;
+  static_assert(T::NW * NO * 256 <= 2 * T::STAGEB, "the states are exchanged through the ring");
+  static_assert(!PLAN || (KT == kF32KT && T::NW == kF32Waves), "the plan's tiles and wavefronts");
+  static_assert(T::QB <= T::STAGEB, "the query rows take the second stage's place");
   __shared__ __attribute__((aligned(1024))) char ring_raw[2 * T::STAGEB];
-  __shared__ float sh_m[kF32Waves][16], sh_l[kF32Waves][16];
+  __shared__ float sh_m[T::NW][16], sh_l[T::NW][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kgrp = lane >> 4;
-  const int ks = wave & 3, mt = wave >> 2;  // key slot, m-tile of the group
+  const int ks = wave % NK, mt = wave / NK;  // key slot, m-tile of the group
   char SDB_LDS *ring = (char SDB_LDS *)(SDB_LDS void *)ring_raw;
 
-  // load-to-LDS: this wavefront's rows of a tile, all of K (wavefronts 0-7) or all of V; K swizzled
-  const bool isv = wave >= kF32Waves / 2;
+  // load-to-LDS: this wavefront's rows of a tile, all of K (the first half of them) or all of V; K swizzled
+  const bool isv = wave >= T::NW / 2;
   const int row0 = (wave * T::LPW - (isv ? T::LPI : 0)) * T::RPI + lane / T::CPR;
   // operand addresses within a stage
   const unsigned lbase = (unsigned)(uintptr_t)ring + ks * 16 * T::ROWB;
@@ -162,10 +196,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
   const unsigned va = lbase + T::TILEB + kgrp * 4 * T::ROWB + l16 * 16;
 
   F32Item it;
-  if (!f32_item(a, blockIdx.x, it)) return;
+  if (PLAN ? !f32_item(a, blockIdx.x, it) : !f32_whole_item(a, blockIdx.x, it)) return;
   const int s = it.s, g = it.g, ctx = it.ctx, qoff = it.qoff;
-  const int k0 = (int)((long long)it.tiles * it.split / it.nsplit) * kF32KT;
-  const int k1 = min((int)((long long)it.tiles * (it.split + 1) / it.nsplit) * kF32KT, ctx + it.B);
+  const int k0 = PLAN ? (int)((long long)it.tiles * it.split / it.nsplit) * KT : 0;
+  const int k1 = PLAN ? min((int)((long long)it.tiles * (it.split + 1) / it.nsplit) * KT, ctx + it.B) : ctx + it.B;
   const int M = a.G * it.B;
   const int m0 = it.grp * it.gmt * 16;          // the group's first query row
   const int m = m0 + mt * 16 + l16;             // this lane's
@@ -180,15 +214,15 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
     for (int q = 0; q < T::LPW; ++q) {  // rows past the item's last key re-read it
       const int row = row0 + q * T::RPI;
       const int col = ((lane % T::CPR) ^ (isv ? 0 : row % 16)) * 16;
-      __builtin_amdgcn_global_load_lds((const void *)(src + (size_t)min(k0 + t * kF32KT + row, k1 - 1) * T::ROWB + col),
+      __builtin_amdgcn_global_load_lds((const void *)(src + (size_t)min(k0 + t * KT + row, k1 - 1) * T::ROWB + col),
                                        (SDB_LDS void *)(st + q * 1024), 16, 0, kLoadNT);
     }
   };
-  const int ntiles = (k1 - k0 + kF32KT - 1) / kF32KT;
+  const int ntiles = (k1 - k0 + KT - 1) / KT;
   // The query rows come the same way, into the second stage and laid out as K rows, before the first
   // tile (plain loads would be waited for together with every transfer in flight).
   {
-    constexpr int QPW = (kF32GroupMT * 16 / T::RPI) / kF32Waves;  // transfers per wavefront
+    constexpr int QPW = (kF32GroupMT * 16 / T::RPI) / T::NW;  // transfers per wavefront
 #pragma unroll
     for (int q = 0; q < QPW; ++q) {
       const int row = (wave * QPW + q) * T::RPI + lane / T::CPR;  // rows past the block re-read its last
@@ -217,7 +251,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
     else wait_vmcnt<0>();
     __syncthreads();  // tile t landed for every wavefront
     const unsigned so = (t & 1) * T::STAGEB;
-    const int kb = k0 + t * kF32KT + ks * 16;
+    const int kb = k0 + t * KT + ks * 16;
     const bool on = act && kb < k1;  // uniform: the last tile may have no key for this slot
     // p[r]: key kb + 4 kgrp + r of row l16; two chains of products
     f32x4 p{0.f, 0.f, 0.f, 0.f}, p1 = p, v[4][NH];
@@ -270,7 +304,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
           oacc[h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][h][i], p[r], oacc[h][i], 0, 0, 0);
   }
 
-  // ---- the four slots' states to one: common maximum, then the scaled sums through LDS ----
+  // ---- the slots' states to one: common maximum, then the scaled sums through LDS ----
   {
     const float2 p16 = pair_x16(l_run);
     const float2 p32 = pair_x32(p16.x + p16.y);
@@ -284,10 +318,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
   float *xch = reinterpret_cast<float *>(ring_raw);  // [wave][h][r][i][lane]
   float mx = -INFINITY, ls = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) mx = fmaxf(mx, sh_m[mt * 4 + w][l16]);
+  for (int w = 0; w < NK; ++w) mx = fmaxf(mx, sh_m[mt * NK + w][l16]);
   const float mu = (mx == -INFINITY) ? 0.f : mx;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) ls = fmaf(sh_l[mt * 4 + w][l16], fast_exp2(sh_m[mt * 4 + w][l16] - mu), ls);
+  for (int w = 0; w < NK; ++w) ls = fmaf(sh_l[mt * NK + w][l16], fast_exp2(sh_m[mt * NK + w][l16] - mu), ls);
   if (act) {
     const float f = fast_exp2(m_run - mu);
 #pragma unroll
@@ -298,20 +332,23 @@ __global__ __launch_bounds__(64 * kF32Waves) void block_attn_f32_kernel(AttnArgs
         for (int r = 0; r < 4; ++r) xch[(wave * NO + (h * 4 + r) * 4 + i) * 64 + lane] = oacc[h][i][r] * f;
   }
   __syncthreads();
-  if (valid) {  // slot ks finishes the dims 64 h + 16 kgrp + 4 ks .. +3 of the m-tile's rows
+  if (valid) {  // slot ks finishes the dims 64 h + 16 kgrp + 4 r .. +3 of the m-tile's rows, r = ks, ks + NK ..
     const bool direct = it.nsplit == 1;
     const size_t prow = (size_t)it.slot * a.part_rows + mt * 16 + l16;
     float *dst = direct ? reinterpret_cast<float *>(reinterpret_cast<char *>(a.out) + qrow_off(m)) : a.part_o + prow * D;
     const float inv = direct ? 1.f / ls : 1.f;
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      f32x4 o{0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < NH; ++h)
 #pragma unroll
-      for (int w = 0; w < 4; ++w)
+      for (int r0 = 0; r0 < 4; r0 += NK) {
+        const int r = r0 + ks;
+        f32x4 o{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] += xch[((mt * 4 + w) * NO + (h * 4 + ks) * 4 + i) * 64 + lane];
-      *reinterpret_cast<f32x4 *>(dst + h * 64 + (kgrp * 4 + ks) * 4) = o * inv;
-    }
+        for (int w = 0; w < NK; ++w)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] += xch[((mt * NK + w) * NO + (h * 4 + r) * 4 + i) * 64 + lane];
+        *reinterpret_cast<f32x4 *>(dst + h * 64 + (kgrp * 4 + r) * 4) = o * inv;
+      }
     if (!direct && ks == 0 && kgrp == 0) a.part_ml[prow] = float2{mx, ls};
   }
 }

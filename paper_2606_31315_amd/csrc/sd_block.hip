@@ -73,6 +73,7 @@ struct AttnPlan {
   // fp32: m-tiles per group at most, groups of the largest block, rows of a partial slot, and the
   // workspace of the plan before this one (even splits): a caller's of that size is still taken
   int group_mt, groups, part_rows;
+  int whole;  // fp32: no pair is split (the two-slot kernel)
   size_t min_total;
   int ve;   // bf16 with one m-tile per wavefront and blocks of 7-8 m-tiles: early V^T reads (VE)
   size_t off_ml, off_o, total;
@@ -180,6 +181,7 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   p->MT = nmt <= 8 ? 1 : 2;  // bf16: 8 wavefronts, 1 or 2 m-tiles each
   p->ve = sh->dtype == SD_BF16 && nmt >= 7 && nmt <= 8;
   p->part_rows = p->Mpad;
+  p->whole = 0;
   size_t off = 0;
   p->off_ml = off;
   if (p->max_splits > 1) off = align256(off + (size_t)slots * p->Mpad * sizeof(float2));
@@ -187,13 +189,16 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   if (p->max_splits > 1) off = align256(off + (size_t)slots * p->Mpad * D * sizeof(float));
   p->total = p->min_total = off > 0 ? off : 256;
   if (f32) {
-    // Balanced shares of the pairs' m-tile groups wherever that gives a CU more than whole pairs would:
-    // at most kBalGrid workgroups, whose slots are the workspace.
     p->groups = (nmt + sdb::kF32GroupMT - 1) / sdb::kF32GroupMT;
     p->group_mt = (nmt + p->groups - 1) / p->groups;
     p->part_rows = p->group_mt * 16;
     const long long tiles = (max_L + sdb::kF32KT - 1) / sdb::kF32KT;
-    p->bal = pairs > 0 && tiles > kBalMinTilesF32 && pairs * p->groups * tiles * sdb::kF32GroupMT <= (1LL << 30);
+    // Whole pairs up to 192 keys, and up to 1024 with more groups than CUs, whose shares would cut few pairs
+    // (both sides measured: attn_f32.hpp).
+    p->whole = max_L <= 192 || (pairs * p->groups > kBalGrid && max_L <= 1024);
+    // Else balanced shares of the pairs' m-tile groups, at most kBalGrid workgroups, whose slots are the
+    // workspace.
+    p->bal = !p->whole && pairs > 0 && tiles > kBalMinTilesF32 && pairs * p->groups * tiles * sdb::kF32GroupMT <= (1LL << 30);
     if (p->bal) p->total = std::max(p->min_total, f32_bytes(*p, pairs, D, kBalGrid));
   }
   return ok();
@@ -201,12 +206,16 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
 
 // fp32: the split kernel, and the merge where pairs may be split.
 template <int D>
-void launch_attn_f32(const sdb::AttnArgs &a, hipStream_t st) {
+void launch_attn_f32(const sdb::AttnArgs &a, hipStream_t st, bool whole) {
   // at most bal_grid splits wherever the pairs are fewer than about half of that (f32_item), else no
   // more than one more per pair
   const int pairs = a.S * a.Hkv * a.groups;
   const int grid = a.bal ? (31 * pairs <= 15 * a.bal_grid ? a.bal_grid : a.bal_grid + pairs) : pairs;
-  hipLaunchKernelGGL((sdb::block_attn_f32_kernel<D>), dim3(grid), dim3(64 * sdb::kF32Waves), 0, st, a);
+  if (whole) {
+    hipLaunchKernelGGL((sdb::block_attn_f32_kernel<D, 2>), dim3(grid), dim3(64 * sdb::kF32Waves / 2), 0, st, a);
+    return;
+  }
+  hipLaunchKernelGGL((sdb::block_attn_f32_kernel<D, 4>), dim3(grid), dim3(64 * sdb::kF32Waves), 0, st, a);
   if (!a.bal) return;
   constexpr int RB = 256 / (D / 4);
   const int nrb = (a.Mpad + RB - 1) / RB;
@@ -525,8 +534,8 @@ int sd_block_attn(const sd_attn_shape *sh, const void *q, const void *k_cache, c
   hipStream_t st = (hipStream_t)stream;
   const bool d128 = sh->head_dim == 128;
   if (sh->dtype == SD_F32) {
-    if (d128) launch_attn_f32<128>(a, st);
-    else launch_attn_f32<64>(a, st);
+    if (d128) launch_attn_f32<128>(a, st, p.whole);
+    else launch_attn_f32<64>(a, st, p.whole);
   } else if (p.bal) {
     if (d128) launch_attn_bal<128>(a, p.MT, st, p.ve);
     else launch_attn_bal<64>(a, p.MT, st, p.ve);

@@ -307,3 +307,18 @@ def test_f32_plan_edges(S, Hq, Hkv, D, ctx, B, mask):
     small = G.run_attn(p, workspace=torch.empty(need, dtype=torch.uint8, device=G.dev())).cpu()
     # each within 1e-5 of the oracle
     assert (full - small).abs().max().item() <= 2e-5
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,Hq,Hkv,ctx,B,mask", [
+    (3, 4, 4, [14, 15, 16], [1, 1, 1], CAUSAL),                    # 16-key slots: short by one, full, one past
+    (4, 4, 1, [15, 28, 29, 0], [16, 4, 4, 9], BIDIR),              # 32-key tiles: the same; 4 m-tiles at most
+    (2, 4, 1, [128, 120], [64, 50], CAUSAL),                       # 192 keys, the longest; 16 and 13 m-tiles, four groups
+    (2, 4, 1, [129, 0], [64, 1], CAUSAL),                          # 193: the splits
+    (65, 8, 4, [(101 * i) % 1010 for i in range(64)] + [1015], [1 + i % 9 for i in range(65)], BIDIR),  # 260 groups, 1024 keys
+    (33, 16, 8, [(67 * i) % 700 for i in range(33)], [i % 40 for i in range(33)], CAUSAL),  # 264 pairs, two groups, empty blocks
+])
+def test_f32_whole_pairs_edges(S, Hq, Hkv, D, ctx, B, mask):
+    """The fp32 kernel without splits (at most 192 keys, or 1024 with more than 256 groups) at the edges of
+    its slots, tiles, groups and rule; rows past a sequence's keys are NaN in the cache."""
+    G.check_attn(_f32(31 + S, S, Hq, Hkv, D, ctx, B, mask))
