@@ -434,8 +434,8 @@ __global__ __launch_bounds__(64 * kFirstWaves) void policy_first_kernel(FirstArg
 
 // h1 = relu(W1 p + b1) from the chunk partials.  Grid (prompt, 64 rows): the four wavefronts take the
 // chunks in turn, a row per lane.  An infinite weight times a piece that is 0 is NaN above though its
-// product with p is not: a NaN row of a prompt whose softmax is sound is summed again here, p times
-// the weight, element by element.
+// product with p is not, and sums of large weights may overflow before the normaliser: a row that is not
+// finite, of a prompt whose softmax is sound, is summed again here, p times the weight, element by element.
 struct MergeArgs {
   const float *part;    // [nch, P, H]
   const float2 *stats;  // [nch, P]
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(256) void policy_merge_kernel(MergeArgs a) {
   __syncthreads();
   if (wave) return;
   y = ((sh_y[0][lane] + sh_y[1][lane]) + (sh_y[2][lane] + sh_y[3][lane])) * inv;
-  unsigned long long bad = __ballot(y != y && inv > 0.f && inv < INFINITY && fabsf(M) < INFINITY && n < a.H);
+  unsigned long long bad = __ballot(!(fabsf(y) < INFINITY) && inv > 0.f && inv < INFINITY && fabsf(M) < INFINITY && n < a.H);
   while (bad) {
     const int l = __ffsll((long long)bad) - 1;
     bad &= bad - 1;

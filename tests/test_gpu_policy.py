@@ -107,3 +107,18 @@ def test_matrix_layers_special_values():
     assert np.array_equal(np.isnan(sc), np.isnan(dense)) and np.array_equal(np.isinf(sc), np.isinf(dense))
     fin = np.isfinite(dense)
     assert np.allclose(sc[fin], dense[fin], rtol=2e-4, atol=2e-4)
+
+
+def test_matrix_layers_large_weights():
+    """Weights near the largest bf16: sums over a chunk overflow before softmax's normaliser, the layer's
+    output does not.  The dense kernels' values."""
+    P, V, H = 6, 4096, 64
+    pp = W.make_policy(98, P=P, V=V, H=H, radius=2, dtype="bf16")
+    pp.w1[5, :] = 3e38
+    pp.w1[6, ::2] = -3e38
+    pp.w1[40, 17:1900] = 2e38
+    dense, _ = _call(pp, _dense_bytes(P, H))
+    sc, _ = _call(pp)
+    assert np.isfinite(dense).all() and np.isfinite(sc).all()
+    # fp32 sums of the same products in another order, as in _check
+    assert (np.abs(sc - dense) <= 2e-4 * np.abs(dense).max()).all()
