@@ -402,11 +402,19 @@ int policy_plan(const sd_policy_shape *sh, PolicyPlan *p) {
   p->off_h2 = off;
   off = align256(off + P * sh->hidden * sizeof(float));
   p->total = off > 0 ? off : 256;
-  // From three prompts on, or where W1's rows are whole 128-byte lines, the matrix cores' first layer
-  // is the faster one (us per call, dense / matrix, H = 2048: V = 151936 P = 1 122.0 / 106.3, P = 8
-  // 294 / 108.6, V = 32000 P = 1 38.2 / 36.1; rows off the lines: V = 100008 P = 1 86.3 / 97.2, V = 50000
-  // P = 2 55.3 / 57.5; H = 1000, V = 30000: P = 1 20.5 / 27.5, P = 3 30.9 / 28.7).
-  p->matrix = P > 2 || sh->vocab % sdb::kFirstKT == 0;
+  // The dense kernels' time grows with the prompts (1, 2, 4 or 8 at a time), the matrix layers' does not, but
+  // their start, merge and second layer take some 6 us more.  So the matrix layers run from five prompts
+  // on; with three or four from 16384 elements (8192 with more than two groups of 512 rows), or 24576 where
+  // W1's rows are not whole 128-byte lines (which the matrix layers read in pieces); with fewer from 60000 whose rows are whole lines, but not
+  // on strides of 128 KB, where a tile's rows meet in few memory channels.  us per call, dense / matrix, inputs not
+  // in a cache: H = 1024, P = 1 and V = 1024 11.3 / 18.4, 32000 27.3 / 26.5 (W1 in the cache 20.8 / 24.1), 151936
+  // 83.1 / 60.1; P = 4 and V = 8192 20.8 / 20.0 (16.6 / 18.3; H = 1536 24.6 / 21.6, 20.1 / 19.7), 32000 36.8 / 27.5; P = 16 and V = 1024 35.0 / 22.8;
+  // H = 2048, P = 1, V = 151936 121.4 / 104.2; off the lines V = 100008 88.5 / 99.
+  // dense over matrix time, P = 1 at V = 57344 / 61440 / 65536 / 65600: H = 512 1.20 / 1.26 / 1.28 / 1.28, H = 2048
+  // 1.07 / 1.10 / 1.07 / 1.11, H = 4096 1.12 / 1.15 / 0.76 / 1.13 (131072, H = 2048: 0.81).
+  const bool lines = sh->vocab % sdb::kFirstKT == 0;
+  p->matrix = P > 4 || (P > 2 && sh->vocab >= (!lines ? 24576 : sh->hidden > 2 * sdb::kFirstRows ? 8192 : 16384)) ||
+              (lines && sh->vocab >= 60000 && sh->vocab % 65536 != 0);
   // chunks: one workgroup per CU (its ring fills the LDS), two tiles or more each
   const int groups = (sh->hidden + sdb::kFirstRows - 1) / sdb::kFirstRows;
   const int tiles = (sh->vocab + sdb::kFirstKT - 1) / sdb::kFirstKT;

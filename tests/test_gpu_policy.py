@@ -122,3 +122,19 @@ def test_matrix_layers_large_weights():
     assert np.isfinite(dense).all() and np.isfinite(sc).all()
     # fp32 sums of the same products in another order, as in _check
     assert (np.abs(sc - dense) <= 2e-4 * np.abs(dense).max()).all()
+
+
+# On both sides of the rule that chooses between the dense and the matrix layers, and the matrix layers' edges
+# (vocabularies below, at and past a tile; partial row groups) at prompt counts that take them.
+@pytest.mark.parametrize("P,V,H,dtype", [(1, 59968, 72, "bf16"), (1, 60032, 72, "f32"), (2, 60008, 24, "bf16"),
+                                         (1, 65536, 8, "bf16"), (2, 65600, 520, "bf16"), (3, 16320, 64, "bf16"),
+                                         (3, 16384, 520, "f32"), (4, 8192, 1032, "bf16"),
+                                         (4, 8128, 1032, "bf16"), (4, 8192, 1024, "f32"), (4, 24568, 24, "bf16"), (4, 24584, 72, "bf16"),
+                                         (5, 64, 8, "bf16"), (5, 8, 8, "f32"), (6, 72, 24, "bf16"), (8, 2040, 1032, "bf16"),
+                                         (5, 4160, 512, "f32"), (7, 1000, 64, "bf16")])
+def test_layers_rule_edges(P, V, H, dtype):
+    pp = W.make_policy(120 + P, P=P, V=V, H=H, radius=2, dtype=dtype)
+    sc, _ = _check(pp)
+    dense, _ = _call(pp, _dense_bytes(P, H))
+    # both within the fp64 oracle's band of 1e-4 + 1e-4 |o|, so within twice that of each other
+    assert (np.abs(sc - dense) <= 2e-4 + 2e-4 * np.abs(dense)).all()
