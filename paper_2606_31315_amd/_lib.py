@@ -467,9 +467,11 @@ def accept(target_logits: torch.Tensor, draft_logits: Optional[torch.Tensor], dr
     if next_token is None:
         next_token = torch.empty(S, dtype=torch.int32, device=dev)
     temperature = float(temperature)
-    shape, ref, nbytes = _cached_call(("accept", S, V, total_q, int(max_block), target_logits.dtype, temperature),
+    # the workspace depends on whether the temperature is above 0 in fp32: one entry for all that are
+    kind = 1.0 if temperature >= 2.0 ** -126 else temperature
+    shape, ref, nbytes = _cached_call(("accept", S, V, total_q, int(max_block), target_logits.dtype, kind),
                                       lambda: accept_shape(target_logits, S, max_block),
-                                      lambda sh: accept_workspace_size(sh, temperature))
+                                      lambda sh: accept_workspace_size(sh, kind))
     if workspace is None:  # a caller's workspace is checked against the need by the library
         workspace = _default_ws.get(nbytes, dev)
     _check(lib().sd_accept(ref, target_logits.data_ptr(), _ptr(draft_logits if sample else None), _ptr(draft_tokens),

@@ -421,3 +421,23 @@ def test_binding_still_names_what_is_wrong_on_the_device():
         a[i] = bad
         with pytest.raises(err):
             sd.accept(*a, 1.0, max_block=p.max_block)
+
+
+def test_binding_keeps_one_plan_for_every_temperature():
+    """A temperature that changes from call to call adds no entry per value to the call cache; 0, and a
+    positive one that is 0 in fp32, are greedy."""
+    import paper_2606_31315_amd as sd
+    from paper_2606_31315_amd import _lib
+    p = _many_seq_problem(42, 3, 1009, (2, 6), "f32", 1.0, name="binding_T")
+    d = G.accept_to_device(p)
+    args = [d["t"], d["d"], d["tok"], d["u"], d["bl"], d["off"]]
+    _lib._call_cache.clear()
+    for i in range(40):
+        sd.accept(*args, 0.5 + i / 64, max_block=p.max_block)
+    assert len(_lib._call_cache) == 1
+    greedy = sd.accept(*args, 0.0, max_block=p.max_block)
+    tiny = sd.accept(*args, 1e-60, max_block=p.max_block)
+    assert all(torch.equal(a, b) for a, b in zip(greedy, tiny))
+    for bad in (-1.0, float("inf"), float("nan")):
+        with pytest.raises(_lib.SdError, match="temperature"):
+            sd.accept(*args, bad, max_block=p.max_block)
