@@ -441,3 +441,17 @@ def test_binding_keeps_one_plan_for_every_temperature():
     for bad in (-1.0, float("inf"), float("nan")):
         with pytest.raises(_lib.SdError, match="temperature"):
             sd.accept(*args, bad, max_block=p.max_block)
+
+
+def test_binding_quick_test_takes_calls_without_drafts(monkeypatch):
+    """Blocks of one row (no draft logits) and drafted tokens with spare entries pass the quick test alone."""
+    import paper_2606_31315_amd as sd
+    from paper_2606_31315_amd import _lib
+    p = _many_seq_problem(43, 5, 1003, (1, 1), "f32", 1.0, name="binding_no_drafts")
+    d = G.accept_to_device(p)
+    ref = sd.accept(d["t"], d["d"], d["tok"], d["u"], d["bl"], d["off"], 1.0, max_block=1)
+    monkeypatch.setattr(_lib, "_accept_checks", None)
+    for draft in (d["d"], None):
+        for tok in (d["tok"], torch.zeros(7, dtype=torch.int32, device=G.dev())):
+            got = sd.accept(d["t"], draft, tok, d["u"], d["bl"], d["off"], 1.0, max_block=1)
+            assert all(torch.equal(a, b) for a, b in zip(ref, got))
