@@ -207,7 +207,8 @@ int sd_accept_workspace_size(const sd_accept_shape *shape, float temperature, si
  * Every path gives identical results.  The single launches need their waiting workgroups
  * resident; a wait that gives up (after about a second, e.g. when other work holds the device)
  * writes -1: at T = 0 its sequence reports -1 in accept_len and next_token, at T > 0 in one or
- * both (an output that is not -1 is exact).
+ * both (an output that is not -1 is exact).  With four chunks per workgroup a wait that gives up
+ * makes the missing sums itself, and every output is exact.
  * Errors: SD_ERR_INVALID_ARG, SD_ERR_WORKSPACE (smaller than the multi-launch path needs),
  * SD_ERR_HIP.  S == 0 returns SD_OK.
  */

@@ -1402,7 +1402,9 @@ __global__ __launch_bounds__(256, 4) void accept_draw_kernel(AcceptArgs a) {
 // the workgroups the device holds at once: grid = (sequence, group of consecutive chunks).  Every
 // chunk's sums are made and filed as above, all of a workgroup's loads in flight together; the
 // workgroup that owns the chosen chunk then takes that chunk's masses again from the vectors it
-// kept, and scans and walks it as above.  Results agree bit for bit.  32 sequences at V = 151936 (2400
+// kept, and scans and walks it as above.  Results agree bit for bit.  A workgroup whose wait gives up
+// makes every chunk's sums of its sequence itself and draws from them, so that these batches, like the
+// three launches they took before, always get the exact values.  32 sequences at V = 151936 (2400
 // chunks, 608 workgroups), T = 1: 12.8 us against 10.4 + 4.8 for the mass and locate launches, 61.2 us per
 // call against 63.0; what is left over a chunk per workgroup's 7.7 us is the rows' 19 MB.
 constexpr int kDrawChunks = 4;
@@ -1415,6 +1417,7 @@ __global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a)
   __shared__ float sh_em[2][2][2 * VEC];  // [head, tail][residual, p] masses of the scalar elements
   __shared__ double sh_cex, sh_tgt;
   __shared__ int sh_kc, sh_usep, sh_ok, sh_hit, sh_last[NW];
+  __shared__ float sh_all[2][64 * kLocSums];  // a wait that gave up: every chunk's sums
   const int ngrp = (a.nch2 + K - 1) / K;
   const int s = blockIdx.x / ngrp, grp = blockIdx.x - s * ngrp, c0 = grp * K;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1433,19 +1436,21 @@ __global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a)
   // ---- every chunk's vector of this thread, loaded together ----
   u32x4 tb[K], qb[K];
   RowChunk chs[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    tb[k] = qb[k] = u32x4{0u, 0u, 0u, 0u};
-    const RowChunk ch = chs[k] = row_chunk<VEC, true>(ta0, a.V, min(c0 + k, a.nch2 - 1), a.nch2);
+  auto load = [&](int c, u32x4 &tv, u32x4 &qv) {
+    tv = qv = u32x4{0u, 0u, 0u, 0u};
+    const RowChunk ch = row_chunk<VEC, true>(ta0, a.V, c, a.nch2);
     const int nvc = (int)(ch.ve - ch.vb);  // <= 256: one vector per thread
     if (nvc > 0) {  // clamped: no per-load branch
       const unsigned r = (unsigned)min(tid, nvc - 1);
-      tb[k] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.target) + (ch.vb + r) * 16);
+      tv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.target) + (ch.vb + r) * 16);
       if (residual && dvec)
-        qb[k] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.draft) +
-                                                 (ch.vb + r + (da0 - ta0) / VEC) * 16);
+        qv = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(a.draft) +
+                                              (ch.vb + r + (da0 - ta0) / VEC) * 16);
     }
-  }
+    return ch;
+  };
+#pragma unroll
+  for (int k = 0; k < K; ++k) chs[k] = load(min(c0 + k, a.nch2 - 1), tb[k], qb[k]);
   // masses of this thread's vector of chunk c: accept_mass_kernel's, element by element
   auto masses = [&](const RowChunk &ch, const u32x4 &tv, const u32x4 &qv, float (&mr)[VEC], float (&mp)[VEC]) {
     float t[VEC], q[VEC];
@@ -1459,13 +1464,10 @@ __global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a)
 #pragma unroll
     for (int i = 0; i < VEC; ++i) elem_masses(t[i], q[i], sp, residual, mr[i], mp[i]);
   };
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int c = c0 + k;
-    if (c >= a.nch2) break;  // uniform
-    const RowChunk ch = chs[k];
+  // a chunk's sums by wavefront, and the masses of its scalar elements
+  auto sums = [&](const RowChunk &ch, const u32x4 &tv, const u32x4 &qv, double *out_r, double *out_p) {
     float mr[VEC], mp[VEC], sr = 0.f, spm = 0.f, vr = 0.f, vp = 0.f;
-    masses(ch, tb[k], qb[k], mr, mp);
+    masses(ch, tv, qv, mr, mp);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
       vr += mr[i];
@@ -1493,9 +1495,14 @@ __global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a)
     scalars(ch.tb, ch.te, 1);
     const float wr = wave_sum_f(sr), wp = wave_sum_f(spm);
     if (lane == 0) {
-      sh_r[k][wave] = wr;
-      sh_p[k][wave] = wp;
+      out_r[wave] = wr;
+      out_p[wave] = wp;
     }
+  };
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (c0 + k >= a.nch2) break;  // uniform
+    sums(chs[k], tb[k], qb[k], sh_r[k], sh_p[k]);
   }
   __syncthreads();
   static_assert(K * 2 * kSumReplicas <= 256, "one word of one copy of one chunk per thread");
@@ -1509,46 +1516,62 @@ __global__ __launch_bounds__(256, 4) void accept_draw_multi_kernel(AcceptArgs a)
   }
 
   // ---- every chunk sum of the sequence, then the chunk search ----
+  auto pick = [&](auto chunk_sums) {
+    const ChunkPick cp = chunk_search(chunk_sums, (a.nch2 + 63) / 64, (double)si1.z);
+    if (lane == 0) {
+      sh_kc = cp.kc;
+      sh_cex = cp.cex;
+      sh_tgt = cp.tgt;
+      sh_usep = cp.use_p;
+    }
+  };
   if (wave == 0) {
     double2 cm[kLocSums];
     const bool ok = poll_chunk_sums_n(a, s, grp % kSumReplicas, cm);
-    if (ok) {
-      const ChunkPick cp = chunk_search([&](int k) { return pick_sums(cm, k); }, (a.nch2 + 63) / 64,
-                                        (double)si1.z);
-      if (lane == 0) {
-        sh_kc = cp.kc;
-        sh_cex = cp.cex;
-        sh_tgt = cp.tgt;
-        sh_usep = cp.use_p;
-      }
-    }
+    if (ok) pick([&](int k) { return pick_sums(cm, k); });
     if (lane == 0) {
       sh_ok = ok;
       sh_hit = 0;
     }
   }
   __syncthreads();
-  if (!sh_ok) {
-    if (tid == 0) {
-      a.accept_len[s] = -1;
-      a.next_token[s] = -1;
+  RowChunk ch;
+  u32x4 tv, qv;
+  if (sh_ok) {  // uniform
+    const int kk = sh_kc - c0;
+    if (kk < 0 || kk >= K) return;
+    ch = chs[0];
+    tv = tb[0];
+    qv = qb[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k)
+      if (k == kk) {  // uniform
+        ch = chs[k];
+        tv = tb[k];
+        qv = qb[k];
+      }
+  } else {  // the wait gave up: every chunk's sums here, and the draw; who else draws writes the same
+    for (int c = 0; c < a.nch2; ++c) {
+      const RowChunk cc = load(c, tv, qv);
+      sums(cc, tv, qv, sh_r[0], sh_p[0]);
+      __syncthreads();
+      if (tid < 2) {
+        const double *x = tid ? sh_p[0] : sh_r[0];
+        sh_all[tid][c] = (float)(x[0] + x[1] + x[2] + x[3]);
+      }
+      __syncthreads();
     }
-    return;
+    if (wave == 0)
+      pick([&](int k) {
+        const int c = 64 * k + lane;
+        return c < a.nch2 ? double2{(double)sh_all[0][c], (double)sh_all[1][c]} : double2{0.0, 0.0};
+      });
+    __syncthreads();
+    ch = load(sh_kc, tv, qv);
   }
-  const int kc = sh_kc, kk = kc - c0;
-  if (kk < 0 || kk >= K) return;
 
   // ---- the chosen chunk: its masses again, their prefixes, and the walk ----
   const bool use_q = residual && !sh_usep;
-  RowChunk ch = chs[0];
-  u32x4 tv = tb[0], qv = qb[0];
-#pragma unroll
-  for (int k = 1; k < K; ++k)
-    if (k == kk) {  // uniform
-      ch = chs[k];
-      tv = tb[k];
-      qv = qb[k];
-    }
   const bool has = tid < (int)(ch.ve - ch.vb);
   float mr[VEC], mp[VEC], mm[VEC];
   masses(ch, tv, qv, mr, mp);

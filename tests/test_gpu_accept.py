@@ -455,3 +455,20 @@ def test_binding_quick_test_takes_calls_without_drafts(monkeypatch):
         for tok in (d["tok"], torch.zeros(7, dtype=torch.int32, device=G.dev())):
             got = sd.accept(d["t"], draft, tok, d["u"], d["bl"], d["off"], 1.0, max_block=1)
             assert all(torch.equal(a, b) for a, b in zip(ref, got))
+
+
+@pytest.mark.parametrize("name,make", _MULTI_CASES, ids=[c[0] for c in _MULTI_CASES])
+def test_several_chunks_per_workgroup_exact_when_the_wait_gives_up(name, make):
+    """With the waits cut to one poll, the draw with several chunks per workgroup makes the missing sums
+    itself: every output exact, bit for bit, in every call."""
+    import paper_2606_31315_amd as sd
+    p = make()
+    d = G.accept_to_device(p)
+    _, (alm, ntm) = _both_paths(p, d)
+    try:
+        sd.accept_set_path(0, 1)
+        for _ in range(5):
+            al, nt = G.run_accept(p, d)
+            assert (al == alm).all() and (nt == ntm).all(), (name, al, alm, nt, ntm)
+    finally:
+        sd.accept_set_path(0)
