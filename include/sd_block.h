@@ -107,6 +107,11 @@ int sd_block_attn_workspace_size(const sd_attn_shape *shape, size_t *bytes);
  *   mask_mode       SD_MASK_*
  *   workspace       >= sd_block_attn_workspace_size() bytes, 256-byte aligned
  *
+ * Where a pair's keys are cut, and so the rounding of its sums, depends on the batch's lengths and the
+ * shape, in fp32 on workspace_bytes too: fp32 calls also take a workspace of the size that splits of
+ * equal length would need (SD_ERR_WORKSPACE names it), with fewer cuts.  Results differ by the rounding of
+ * fp32 sums, in bf16 also by that of the attention weights; the same call gives the same bits.
+ *
  * Host-checked preconditions: q, caches and out 16-byte aligned; max_ctx + max_block
  * <= Lmax; total_q <= S * max_block; (Hq/Hkv) * max_block <= 256.
  * Errors: SD_ERR_INVALID_ARG, SD_ERR_UNSUPPORTED (head_dim), SD_ERR_WORKSPACE, SD_ERR_HIP.
@@ -383,6 +388,15 @@ int sd_policy_workspace_size(const sd_policy_shape *shape, size_t *bytes);
  *   block_size   [P] int32 out
  * p and the layer activations are fp32; products accumulate in fp32.  Logits and w1, w2, w3
  * 16-byte aligned; workspace 256-byte aligned, >= sd_policy_workspace_size().
+ *
+ * Paths.  The layers run on matrix cores or on dense vector kernels, by P, V and H (the matrix
+ * cores from five prompts on, for three or four over vocabularies of some 16 thousand and more, for
+ * fewer over some 60 thousand).  A workspace without room for the matrix layers' partial sums is
+ * also taken, down to ceil256(512 P) + 2 ceil256(4 P H) bytes (ceil256: up to a multiple of 256),
+ * and gets the dense kernels; SD_ERR_WORKSPACE below that.  The two sum in different orders, so a
+ * prompt's scores may differ in their last bits, and its block size where two scores tie that
+ * closely, with the prompts it is batched with and with the workspace; the same call gives the same
+ * bits.
  * Errors: SD_ERR_INVALID_ARG, SD_ERR_UNSUPPORTED (vocab or hidden not a multiple of 8),
  * SD_ERR_WORKSPACE, SD_ERR_HIP.  P == 0 returns SD_OK without touching the device.
  */

@@ -11,14 +11,126 @@
 // (m-tiles), so each K/V byte is read from HBM once for the whole group.  A pair whose keys fit one
 // split writes its output directly.  Otherwise each split writes fp32 partials (unnormalised O, row
 // max in log2 units, row sum) and a second launch, block_attn_merge_kernel, combines them.  The kernel
-// boundary is the only cross-workgroup synchronisation: an in-kernel "last workgroup merges" scheme
-// needs agent-scope release fences, which on gfx950 write back the XCD's L2 and cost far
-// more than the second launch.
+// boundary is the only cross-workgroup synchronisation: a release fence per workgroup writes back the
+// XCD's L2, and merging in the split kernel without fences (tagged partials, the last arrivals polling)
+// was slower too, 38.65 against 33.35 us per call on the ragged batch.
+//
+// The plans' arithmetic comes first: plain integers, for the device, for the launchers and, in a build
+// without HIP, for a check of the plans on the CPU.
 #pragma once
 
+#if defined(__HIPCC__)
 #include "common.hpp"
+#define SDB_HD __host__ __device__ __forceinline__
+#else
+#define SDB_HD inline
+#endif
 
 namespace sdb {
+
+SDB_HD int plan_min(int a, int b) { return a < b ? a : b; }
+SDB_HD int plan_max(int a, int b) { return a > b ? a : b; }
+SDB_HD int plan_mtiles(int G, int B) { return (G * plan_max(B, 0) + 15) >> 4; }  // 16-row query tiles of a block
+
+// ---- balanced plan (bf16) ----------------------------------------------------------
+// Relative time of one key tile by the block's m-tiles (16-row query tiles): up to 3 m-tiles
+// the split kernel streams a tile at the memory's pace; beyond that the wavefronts' LDS reads
+// and arithmetic add to it (8 sequences x 8 kv heads, contexts 4096, one wave, MI355X: 33.1 us
+// per call at 2 m-tiles, 33.7 at 3, 34.5 at 4, 35.5 at 5, 37.9 at 6, 40.0 at 7, 41.6 at 8).
+// Chosen by A/B on the multi-wave batches: against the steeper table measured before the
+// kernel's lane swaps (20, 23, 25, 28, 32, 33 for 1-3 ... 8 m-tiles), 16 sequences with contexts
+// 1k-8k 82.75 -> 81.14 us per call, 32 sequences with contexts 8k-32k 472.9 -> 452.1 us.
+constexpr int kBalWeightMax8 = 31;  // the weight at 8 m-tiles; 4 more per m-tile past 8
+SDB_HD int bal_weight(int nmt) {
+  constexpr int kw[9] = {20, 20, 20, 20, 22, 24, 26, 29, kBalWeightMax8};
+  return nmt <= 8 ? kw[nmt] : kBalWeightMax8 + 4 * (nmt - 8);
+}
+
+constexpr int kBalGrid = 256;     // workgroups of the balanced plan: one per CU of the MI355X
+constexpr int kMaxMTiles = 16;    // (Hq / Hkv) * max_block <= 256
+
+// Units a pair takes on the line ahead of its first tile: what starting it costs the workgroup
+// whose share runs on into it (the pair before filed, query rows and first tiles fetched), about five
+// tiles.  Less than the shortest share, so every workgroup between a pair's first and last holds
+// a tile of it.  us per call at 0 / 60 / 90 / 110 / 130 / 160 units: 16 sequences, contexts 1k-8k 64.8 / 62.0 / 61.1 /
+// 60.4 / 60.7 / 62.0; 32 sequences, contexts 8k-32k 451 / 450 / 443 / 445 / 443 / 444; 20 sequences, head_dim
+// 64, contexts 1k-12k 86.8 without, 79.5 / 79.6 / 79.4 at 90 / 110 / 130; 24 sequences, contexts 3k-16k
+// 144.1 without, 141.1 / 142.5 / 143.6.
+constexpr int kBalPairCost = 100;
+// Units per share of W in all.
+SDB_HD int bal_per(int W, int min_tiles) { return plan_max((W + kBalGrid - 1) / kBalGrid, min_tiles * bal_weight(1)); }
+
+// Units of one pair of n tiles of weight w (0: no tiles, no pair).
+SDB_HD int bal_pair_units(int n, int w) { return n > 0 ? n * w + kBalPairCost : 0; }
+
+// First tile of a pair (first tile's unit p0, weight w) whose first unit is at or after unit u.
+SDB_HD int bal_tile_at(int u, int p0, int w) { return u <= p0 ? 0 : (u - p0 + w - 1) / w; }
+
+// What the share [u0, u1) takes of the pair that holds unit u0 (its units from `start` on, ts tiles of
+// weight w): tiles [j0, j1), and the cursor after them; none where the next tile is the next pair's (next:
+// that pair's first unit) or the next share's (next: u1).
+struct BalPiece {
+  int j0, j1, next;
+  bool any;
+};
+SDB_HD BalPiece bal_piece(int u0, int u1, int start, int ts, int w) {
+  const int p0 = start + kBalPairCost;
+  BalPiece b;
+  b.j0 = b.j1 = bal_tile_at(u0, p0, w);
+  b.any = false;
+  if (b.j0 >= ts) {  // past the first unit of the pair's last tile
+    b.next = p0 + ts * w;
+  } else if (p0 + b.j0 * w >= u1) {
+    b.next = u1;
+  } else {
+    b.any = true;
+    b.j1 = plan_min(bal_tile_at(u1, p0, w), ts);  // > j0
+    b.next = p0 + b.j1 * w;
+  }
+  return b;
+}
+
+// First and last share that hold a tile of the pair.
+struct BalShares {
+  int first, last;
+};
+SDB_HD BalShares bal_shares(int start, int ts, int w, int per) {
+  const int p0 = start + kBalPairCost;
+  return BalShares{p0 / per, (p0 + (ts - 1) * w) / per};
+}
+
+// ---- fp32 plan ---------------------------------------------------------------------
+constexpr int kF32KT = 64;       // keys per tile
+constexpr int kF32Waves = 16;    // wavefronts of the split kernel, and candidates of f32_per
+constexpr int kF32GroupMT = 4;   // m-tiles per work item at most
+constexpr int kF32MinTiles = 2;  // shortest share, in tiles
+
+// A block's m-tiles go to groups of at most group_mt (<= 4), evenly: (groups, m-tiles per group).  The
+// host keeps the groups of the largest block to four.
+struct F32Groups {
+  int n, mt;
+};
+SDB_HD F32Groups f32_groups(int nmt, int group_mt) {
+  const int ng = 1 + (nmt > group_mt) + (nmt > 2 * group_mt) + (nmt > 3 * group_mt);
+  const int per = ng == 1 ? nmt : ng == 2 ? (nmt + 1) >> 1 : ng == 3 ? ((nmt + 2) * 43) >> 7 : (nmt + 3) >> 2;
+  return F32Groups{ng, per};
+}
+// Relative time of a tile: the matrix products of a group's m-tiles, 2048 cycles of a SIMD each, or the
+// memory's pace, 64 KB in about three of them.
+SDB_HD int f32_weight(int mt) { return plan_max(mt, 3); }
+// Units per split: candidate k = 0 .. kF32Waves - 1 of the total W, ascending.
+SDB_HD int f32_per0(int W, int grid, int min_tiles) { return plan_max((W + grid - 1) / grid, min_tiles * 3); }
+SDB_HD int f32_per(int per0, int k) { return per0 + ((per0 * k + 15) >> 4); }
+// Splits of a pair's group at `per` units of work each.
+SDB_HD int f32_splits(int tiles, int weight, int per) {
+  const unsigned n = ((unsigned)(tiles * weight) + (unsigned)per - 1u) / (unsigned)per;
+  return plan_min((int)n, tiles);
+}
+// Workgroups that hold every split: the candidates end at per0 x 31 / 16, where the splits number at most
+// 16 / 31 grid + pairs; else none is sure to fit the grid and there are at most as many more as pairs.
+SDB_HD int f32_launch(int pairs, int grid) { return 31 * pairs <= 15 * grid ? grid : grid + pairs; }
+
+#if defined(__HIPCC__)
 
 struct AttnArgs {
   const void *q;
@@ -224,34 +336,6 @@ __device__ __forceinline__ bool attn_item(const AttnArgs &a, int b, AttnItem &it
 // its partial at slot w + q, so a pair's pieces hold consecutive slots from (first workgroup) + q.
 // (Even splits per pair leave ragged batches with fractional waves: 16 sequences, contexts
 // 1k-8k, about 350 splits of up to 2064 keys on 256 CUs.)
-#ifndef SDB_BAL_WEIGHTS
-#define SDB_BAL_WEIGHTS 1
-#endif
-// Relative time of one key tile by the block's m-tiles (16-row query tiles): up to 3 m-tiles
-// the split kernel streams a tile at the memory's pace; beyond that the wavefronts' LDS reads
-// and arithmetic add to it (8 sequences x 8 kv heads, contexts 4096, one wave, MI355X: 33.1 us
-// per call at 2 m-tiles, 33.7 at 3, 34.5 at 4, 35.5 at 5, 37.9 at 6, 40.0 at 7, 41.6 at 8).
-// Chosen by A/B on the multi-wave batches: against the steeper table measured before the
-// kernel's lane swaps (20, 23, 25, 28, 32, 33 for 1-3 ... 8 m-tiles), 16 sequences with contexts
-// 1k-8k 82.75 -> 81.14 us per call, 32 sequences with contexts 8k-32k 472.9 -> 452.1 us.
-constexpr int kBalWeightMax8 = 31;  // the weight at 8 m-tiles; 4 more per m-tile past 8
-__device__ __forceinline__ int bal_weight(int nmt) {
-  if (!SDB_BAL_WEIGHTS) return 1;
-  constexpr int kw[9] = {20, 20, 20, 20, 22, 24, 26, 29, kBalWeightMax8};
-  return nmt <= 8 ? kw[nmt] : kBalWeightMax8 + 4 * (nmt - 8);
-}
-
-constexpr int kBalGrid = 256;  // workgroups of the balanced plan: one per CU of the MI355X
-
-// Units a pair takes on the line ahead of its first tile: what starting it costs the workgroup
-// whose share runs on into it (the pair before filed, query rows and first tiles fetched), about five
-// tiles.  Less than the shortest share, so every workgroup between a pair's first and last holds
-// a tile of it.  us per call at 0 / 60 / 90 / 110 / 130 / 160 units: 16 sequences, contexts 1k-8k 64.8 / 62.0 / 61.1 /
-// 60.4 / 60.7 / 62.0; 32 sequences, contexts 8k-32k 451 / 450 / 443 / 445 / 443 / 444; 20 sequences, head_dim
-// 64, contexts 1k-12k 86.8 without, 79.5 / 79.6 / 79.4 at 90 / 110 / 130; 24 sequences, contexts 3k-16k
-// 144.1 without, 141.1 / 142.5 / 143.6.
-constexpr int kBalPairCost = 100;
-
 struct BalShare {
   int per, u0, u1;  // units per share; this workgroup's unit range [u0, u1)
 };
@@ -261,19 +345,7 @@ __device__ __forceinline__ int bal_seq_tiles(bool live, int ctx, int B, int kt) 
   return (live && B > 0) ? (ctx + B + kt - 1) / kt : 0;
 }
 __device__ __forceinline__ int bal_seq_weight(const AttnArgs &a, int B) {
-  return bal_weight((a.G * max(B, 0) + 15) / 16);
-}
-
-__device__ __forceinline__ int bal_per(const AttnArgs &a, int W) {
-  return max((W + kBalGrid - 1) / kBalGrid, a.bal_min_tiles * bal_weight(1));
-}
-
-// Units of one pair of n tiles of weight w (0: no tiles, no pair).
-__device__ __forceinline__ int bal_pair_units(int n, int w) { return n > 0 ? n * w + kBalPairCost : 0; }
-
-// First tile of a pair (first tile's unit p0, weight w) whose first unit is at or after unit u.
-__device__ __forceinline__ int bal_tile_at(int u, int p0, int w) {
-  return u <= p0 ? 0 : (u - p0 + w - 1) / w;
+  return bal_weight(plan_mtiles(a.G, B));
 }
 
 // This workgroup's share: the total W, one round of loads per 64 sequences.
@@ -287,7 +359,7 @@ __device__ __forceinline__ BalShare bal_share(const AttnArgs &a, int w, int kt) 
     W += __builtin_amdgcn_readlane(wave_scan_i(u), 63);
   }
   BalShare sh;
-  sh.per = bal_per(a, W);
+  sh.per = bal_per(W, a.bal_min_tiles);
   sh.u0 = min(w * sh.per, W);
   sh.u1 = min(sh.u0 + sh.per, W);
   return sh;
@@ -320,31 +392,26 @@ __device__ __forceinline__ bool bal_item(const AttnArgs &a, BalShare &sh, int kt
         const int pu = bal_pair_units(ts, w);  // units of each of the sequence's pairs
         const int pre = __builtin_amdgcn_readlane(incl - sequ, l);
         const int g = (sh.u0 - pre) / pu;
-        const int p0 = pre + g * pu + kBalPairCost;  // first tile's unit of pair (s, g)
-        const int j0 = bal_tile_at(sh.u0, p0, w);
-        if (j0 >= ts) {  // past the first unit of the pair's last tile: the next pair
-          sh.u0 = p0 + ts * w;
+        const int start = pre + g * pu;  // first unit of pair (s, g)
+        const BalPiece b = bal_piece(sh.u0, sh.u1, start, ts, w);
+        sh.u0 = b.next;
+        if (!b.any) {
+          if (b.next >= sh.u1) return false;
           next_pair = true;
           break;
         }
-        if (p0 + j0 * w >= sh.u1) {  // the next tile belongs to the next share
-          sh.u0 = sh.u1;
-          return false;
-        }
-        const int j1 = min(bal_tile_at(sh.u1, p0, w), ts);  // > j0
         it.s = c0 + l;
         it.g = g;
         it.ctx = __builtin_amdgcn_readlane(ctx, l);
         it.B = __builtin_amdgcn_readlane(B, l);
         it.qoff = __builtin_amdgcn_readlane(off, l);
-        it.k0 = j0 * kt;
-        it.k1 = min(j1 * kt, it.ctx + it.B);
-        const int wf = p0 / sh.per, wl = (p0 + (ts - 1) * w) / sh.per;
+        it.k0 = b.j0 * kt;
+        it.k1 = min(b.j1 * kt, it.ctx + it.B);
+        const BalShares bs = bal_shares(start, ts, w, sh.per);
         const int wme = blockIdx.x;  // the piece's first unit lies in this workgroup's share
-        it.nsplit = wl - wf + 1;
-        it.split = wme - wf;
+        it.nsplit = bs.last - bs.first + 1;
+        it.split = wme - bs.first;
         it.slot = wme + it.s * a.Hkv + g;
-        sh.u0 = p0 + j1 * w;
         return true;
       }
       before = __builtin_amdgcn_readlane(incl, 63);
@@ -375,10 +442,9 @@ __device__ __forceinline__ int2 attn_pair_slots(const AttnArgs &a, int s, int g,
     }
     B = Bs;
     if (Bs <= 0) return int2{0, 0};
-    const int per = bal_per(a, W), w = bal_seq_weight(a, Bs);
-    const int p0 = pre + g * bal_pair_units(ts, w) + kBalPairCost;
-    const int wf = p0 / per, wl = (p0 + (ts - 1) * w) / per;
-    return int2{wf + s * a.Hkv + g, wl - wf + 1};
+    const int w = bal_seq_weight(a, Bs);
+    const BalShares bs = bal_shares(pre + g * bal_pair_units(ts, w), ts, w, bal_per(W, a.bal_min_tiles));
+    return int2{bs.first + s * a.Hkv + g, bs.last - bs.first + 1};
   }
   if (!a.dense) {
     // both lengths in one round of scalar loads: one use of both before the branch on B, so the
@@ -410,19 +476,8 @@ __device__ __forceinline__ int2 attn_pair_slots(const AttnArgs &a, int s, int g,
 }
 
 // ---- fp32 plan ---------------------------------------------------------------------
-// A block's m-tiles go to groups of at most a.group_mt (<= 4), evenly: (groups, m-tiles per group).  The
-// host keeps the groups of the largest block to four.
-__device__ __forceinline__ int2 f32_groups(const AttnArgs &a, int B) {
-  const int nmt = (a.G * max(B, 0) + 15) >> 4, gm = a.group_mt;
-  const int ng = 1 + (nmt > gm) + (nmt > 2 * gm) + (nmt > 3 * gm);
-  const int per = ng == 1 ? nmt : ng == 2 ? (nmt + 1) >> 1 : ng == 3 ? ((nmt + 2) * 43) >> 7 : (nmt + 3) >> 2;
-  return int2{ng, per};
-}
-constexpr int kF32KT = 64;  // keys per tile
-
-// A sequence on lane k: key tiles of each of its pairs, the relative time of one (the matrix products of
-// a group's m-tiles, 2048 cycles of a SIMD each, or the memory's pace, 64 KB in about three of them), and
-// its pairs (kv heads x groups; none without a block).
+// A sequence on lane k: key tiles of each of its pairs, the relative time of one, and its pairs (kv heads x
+// groups; none without a block).
 struct F32Seq {
   int ctx, B, off, tiles, weight, pairs;
 };
@@ -433,18 +488,12 @@ __device__ __forceinline__ F32Seq f32_seq(const AttnArgs &a, int k) {
   q.B = a.block_lens[kc];
   q.off = a.q_offsets[kc];
   const bool live = k < a.S && q.B > 0;
-  const int2 gr = f32_groups(a, q.B);
+  const F32Groups gr = f32_groups(plan_mtiles(a.G, q.B), a.group_mt);
   q.tiles = live ? (q.ctx + q.B + kF32KT - 1) / kF32KT : 0;
-  q.weight = max(gr.y, 3);
-  q.pairs = live ? a.Hkv * gr.x : 0;
+  q.weight = f32_weight(gr.mt);
+  q.pairs = live ? a.Hkv * gr.n : 0;
   return q;
 }
-// Splits of a pair at `per` units of work each.
-__device__ __forceinline__ int f32_splits(const F32Seq &q, int per) {
-  const unsigned n = ((unsigned)(q.tiles * q.weight) + (unsigned)per - 1u) / (unsigned)per;
-  return min((int)n, q.tiles);
-}
-
 // Merge of the split partials: workgroup (s, g, row block) combines
 //   O = sum_sp 2^(m_sp - M) O_sp / sum_sp 2^(m_sp - M) l_sp,  M = max_sp m_sp
 // for RB rows of the (sequence, kv head) group, D/4 threads per row, one float4 each.
@@ -472,15 +521,15 @@ __global__ __launch_bounds__(256) void block_attn_merge_kernel(AttnArgs a) {
     ps = int2{0, 0};
     for (int c0 = 0; c0 <= s; c0 += 64) {
       const F32Seq q = f32_seq(a, c0 + lane);
-      const int n = f32_splits(q, per), incl = before + wave_scan_i(n * q.pairs);
+      const int n = f32_splits(q.tiles, q.weight, per), incl = before + wave_scan_i(n * q.pairs);
       if (s < c0 + 64) {
         const int l = s - c0;
         B = __builtin_amdgcn_readlane(q.B, l);
         const int ns = __builtin_amdgcn_readlane(n, l), base = __builtin_amdgcn_readlane(incl - n * q.pairs, l);
-        const int2 gr = f32_groups(a, B);
-        const int grp = min(mw / (16 * max(gr.y, 1)), gr.x - 1);
-        mw -= grp * 16 * gr.y;
-        ps = int2{base + (g * gr.x + grp) * ns, B > 0 ? ns : 0};
+        const F32Groups gr = f32_groups(plan_mtiles(a.G, B), a.group_mt);
+        const int grp = min(mw / (16 * max(gr.mt, 1)), gr.n - 1);
+        mw -= grp * 16 * gr.mt;
+        ps = int2{base + (g * gr.n + grp) * ns, B > 0 ? ns : 0};
       }
       before = __builtin_amdgcn_readlane(incl, 63);
     }
@@ -524,5 +573,7 @@ __global__ __launch_bounds__(256) void block_attn_merge_kernel(AttnArgs a) {
   else
     *reinterpret_cast<f32x4 *>(orow + d * EB) = o;
 }
+
+#endif  // __HIPCC__
 
 }  // namespace sdb

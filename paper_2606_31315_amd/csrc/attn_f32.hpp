@@ -40,9 +40,6 @@
 
 namespace sdb {
 
-constexpr int kF32Waves = 16;
-constexpr int kF32GroupMT = 4;  // m-tiles per work item at most
-
 // NK key slots of 16 keys: a wavefront for each slot and m-tile.
 template <int D, int NK>
 struct F32Tile {
@@ -112,24 +109,24 @@ __device__ __forceinline__ bool f32_item(const AttnArgs &a, int b, F32Item &it) 
       const F32Seq q = c0 == 0 ? first : f32_seq(a, c0 + lane);
       W += __builtin_amdgcn_readlane(wave_scan_i(q.tiles * q.weight * q.pairs), 63);
     }
-    const int per0 = max((W + a.bal_grid - 1) / a.bal_grid, a.bal_min_tiles * 3);
+    const int per0 = f32_per0(W, a.bal_grid, a.bal_min_tiles);
     int n = 0;
-    const int pk = per0 + ((per0 * wave + 15) >> 4);
+    const int pk = f32_per(per0, wave);
     for (int c0 = 0; c0 < a.S; c0 += 64) {
       const F32Seq q = c0 == 0 ? first : f32_seq(a, c0 + lane);
-      n += __builtin_amdgcn_readlane(wave_scan_i(f32_splits(q, pk) * q.pairs), 63);
+      n += __builtin_amdgcn_readlane(wave_scan_i(f32_splits(q.tiles, q.weight, pk) * q.pairs), 63);
     }
     if (lane == 0) sh_n[wave] = n;
     __syncthreads();
     const unsigned long long fit = __ballot(lane < kF32Waves && sh_n[lane & (kF32Waves - 1)] <= a.bal_grid);
     const int k = fit ? __ffsll((long long)fit) - 1 : kF32Waves - 1;
-    per = per0 + ((per0 * k + 15) >> 4);
+    per = f32_per(per0, k);
     if (b == 0 && threadIdx.x == 0) *a.plan = per;
   }
   int before = 0;
   for (int c0 = 0; c0 < a.S; c0 += 64) {
     const F32Seq q = c0 == 0 ? first : f32_seq(a, c0 + lane);
-    const int n = f32_splits(q, per), items = n * q.pairs, incl = before + wave_scan_i(items);
+    const int n = f32_splits(q.tiles, q.weight, per), items = n * q.pairs, incl = before + wave_scan_i(items);
     const unsigned long long hit = __ballot(incl > b && incl - items <= b);
     if (hit) {
       const int l = __ffsll((long long)hit) - 1;  // wave-uniform
@@ -139,13 +136,13 @@ __device__ __forceinline__ bool f32_item(const AttnArgs &a, int b, F32Item &it) 
       it.qoff = __builtin_amdgcn_readlane(q.off, l);
       it.tiles = __builtin_amdgcn_readlane(q.tiles, l);
       it.nsplit = __builtin_amdgcn_readlane(n, l);
-      const int2 gr = f32_groups(a, it.B);
+      const F32Groups gr = f32_groups(plan_mtiles(a.G, it.B), a.group_mt);
       const int r = b - __builtin_amdgcn_readlane(incl - items, l);
       const int p = r / it.nsplit;
       it.split = r - p * it.nsplit;
-      it.g = p / gr.x;
-      it.grp = p - it.g * gr.x;
-      it.gmt = gr.y;
+      it.g = p / gr.n;
+      it.grp = p - it.g * gr.n;
+      it.gmt = gr.mt;
       it.slot = b;
       return true;
     }
@@ -163,11 +160,11 @@ __device__ __forceinline__ bool f32_whole_item(const AttnArgs &a, int b, F32Item
   it.ctx = ld_uniform(a.ctx_lens, it.s);
   it.B = ld_uniform(a.block_lens, it.s);
   it.qoff = ld_uniform(a.q_offsets, it.s);
-  const int2 gr = f32_groups(a, it.B);
-  it.gmt = gr.y;
+  const F32Groups gr = f32_groups(plan_mtiles(a.G, it.B), a.group_mt);
+  it.gmt = gr.mt;
   it.split = it.slot = 0;
   it.nsplit = 1;
-  return it.B > 0 && it.grp < gr.x;
+  return it.B > 0 && it.grp < gr.n;
 }
 
 // NK = 4: f32_item's splits; NK = 2: whole pairs (a.bal = 0).

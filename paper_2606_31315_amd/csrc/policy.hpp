@@ -14,8 +14,8 @@
 //   policy_second_kernel  relu(W2 h1 + b2) on matrix cores.
 //   policy_head_kernel    one workgroup per prompt, one wavefront per candidate: the 2k+1 scores
 //                         and their argmax.
-// Where those do not apply (one or two prompts over rows of W1 that are not whole cache lines; a
-// workspace without room for the chunk partials):
+// Where those are slower or do not apply (few prompts over short rows of W1, or rows that are not whole
+// cache lines: policy_plan; a workspace without room for the chunk partials):
 //   policy_stats_kernel   grid (prompt, chunk): (max, sum exp(z - max)) of one vocabulary chunk,
 //                         one online pass per thread.
 //   policy_dense_kernel   y = act(W x + b) for every prompt: a workgroup owns R rows of W and
@@ -219,8 +219,8 @@ __global__ __launch_bounds__(256) void policy_dense_kernel(DenseArgs a) {
 // units, which falls behind the memory from two prompts on.  Here the first layer runs on
 // v_mfma_f32_16x16x32_bf16 with one column per prompt: W1 is bf16, and an fp32 term is the exact sum
 // of three bf16 numbers, so three products per weight give the fp32 product and the sums stay fp32.
-//   Grid (chunk of the vocabulary, 512 rows of W1), chunk fastest, so that a chunk's workgroups
-//   share an XCD and its L2 holds the chunk's logits.  A workgroup's 8 wavefronts own 64 rows each
+//   Grid (chunk of the vocabulary, 512 rows of W1), chunk fastest: where the chunks are a multiple of 8
+//   a chunk's workgroups share an XCD, whose L2 holds the chunk's logits; elsewhere several XCDs read them.  A workgroup's 8 wavefronts own 64 rows each
 //   and make the terms 2^((z - m) log2 e) of a 64-element tile together, against the chunk's
 //   maximum m (one pass over the chunk's logits while the first tiles are on their way).  No softmax
 //   pass comes first: the workgroup files its partial sums with (m, sum of the terms), and

@@ -69,9 +69,8 @@ constexpr int kBf16KT = SDB_BF16_KT, kBf16NS = SDB_BF16_NS;
 struct AttnPlan {
   int G, KT, split_len, max_splits, Mpad, n_work, per_xcd, grid, dense, MT;
   int bal;  // balanced shares (see bal_share)
-  int bal_grid;
   // fp32: m-tiles per group at most, groups of the largest block, rows of a partial slot, and the
-  // workspace of the plan before this one (even splits): a caller's of that size is still taken
+  // smallest workspace taken (even splits'), which leaves fewer slots or whole pairs
   int group_mt, groups, part_rows;
   int whole;  // fp32: no pair is split (the two-slot kernel)
   size_t min_total;
@@ -79,14 +78,10 @@ struct AttnPlan {
   size_t off_ml, off_o, total;
 };
 
-// Balanced plan: one workgroup per CU (the bf16 split kernel holds a CU), each
-// share at least 16 key tiles (1024 keys), like the shortest split of the other multi-wave plans.
 using sdb::kBalGrid;
-constexpr int kBalMinTiles = 16;
-#ifndef SDB_F32_MIN_TILES
-#define SDB_F32_MIN_TILES 2
-#endif
-constexpr int kBalMinTilesF32 = SDB_F32_MIN_TILES;  // shortest fp32 share, in 64-key tiles
+constexpr int kBalMinTiles = 16;  // balanced plan: shortest share, in tiles of the lightest weight (1024 keys)
+static_assert(sdb::kBalPairCost + sdb::kBalWeightMax8 + 4 * (sdb::kMaxMTiles - 8) < kBalMinTiles * 20,
+              "a pair's start and its heaviest tile together are less than a share");
 
 // Workspace of an fp32 balanced plan of `grid` workgroups.
 size_t f32_bytes(const AttnPlan &p, long long pairs, int D, long long grid) {
@@ -120,9 +115,10 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   p->KT = f32 ? 32 : kBf16KT;
   const long long max_L = (long long)sh->max_ctx + sh->max_block;
   const long long pairs = (long long)S * Hkv;
+  // Even splits, the bf16 kernel's (fp32: these decide only the smallest workspace it takes, with the
+  // two workgroups per CU and 32-key tiles of the kernel they were made for).
   // Split the keys so that, at the maximum length, the grid is one wave: one workgroup per
-  // CU for the bf16 kernel (one 512-thread workgroup fills a CU's LDS ring), two for the fp32
-  // kernel.  A grid just over one wave runs its last workgroups as a tail (measured on the
+  // CU (one 512-thread workgroup fills a CU's LDS ring).  A grid just over one wave runs its last workgroups as a tail (measured on the
   // ragged Qwen3-4B batch: 5 splits of 1024 keys, 48.3 us; 4 splits of 1088, 40.4 us).
   // Splits stay at most 4096 keys so long ragged contexts still spread over several waves.
   // Rounding the split to 16 keys rather than a whole 64-key tile keeps the splits even
@@ -130,8 +126,7 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   const long long target_wgs = (sh->dtype == SD_BF16) ? 256 : 512;
   long long want = pairs > 0 ? target_wgs / pairs : 1;
   if (want < 1) want = 1;
-  // Split lengths are multiples of 16 keys for bf16 (a split's last key tile may be
-  // partial) and of the key tile for fp32.
+  // Split lengths are multiples of 16 keys (a split's last key tile may be partial).
   const int gran = (sh->dtype == SD_BF16) ? 16 : p->KT;
   long long sl = (max_L + want - 1) / want;
   sl = ((sl + gran - 1) / gran) * gran;
@@ -170,7 +165,6 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
   // fused-append calls alike.  Partial slots: one per workgroup and pair a share touches, at
   // most kBalGrid + pairs.
   p->bal = !f32 && p->dense && p->max_splits > 1;
-  p->bal_grid = kBalGrid;
   {  // the device sums tile weights (at most kBalWeightMax8 + 4 per m-tile past 8) in 32-bit integers
     const long long nmt_max = (G * (long long)sh->max_block + 15) / 16;
     const long long wmax = sdb::kBalWeightMax8 + 4 * std::max(0LL, nmt_max - 8);
@@ -198,7 +192,7 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
     p->whole = max_L <= 192 || (pairs * p->groups > kBalGrid && max_L <= 1024);
     // Else balanced shares of the pairs' m-tile groups, at most kBalGrid workgroups, whose slots are the
     // workspace.
-    p->bal = !p->whole && pairs > 0 && tiles > kBalMinTilesF32 && pairs * p->groups * tiles * sdb::kF32GroupMT <= (1LL << 30);
+    p->bal = !p->whole && pairs > 0 && tiles > sdb::kF32MinTiles && pairs * p->groups * tiles * sdb::kF32GroupMT <= (1LL << 30);
     if (p->bal) p->total = std::max(p->min_total, f32_bytes(*p, pairs, D, kBalGrid));
   }
   return ok();
@@ -207,10 +201,8 @@ int attn_plan(const sd_attn_shape *sh, AttnPlan *p) {
 // fp32: the split kernel, and the merge where pairs may be split.
 template <int D>
 void launch_attn_f32(const sdb::AttnArgs &a, hipStream_t st, bool whole) {
-  // at most bal_grid splits wherever the pairs are fewer than about half of that (f32_item), else no
-  // more than one more per pair
   const int pairs = a.S * a.Hkv * a.groups;
-  const int grid = a.bal ? (31 * pairs <= 15 * a.bal_grid ? a.bal_grid : a.bal_grid + pairs) : pairs;
+  const int grid = a.bal ? sdb::f32_launch(pairs, a.bal_grid) : pairs;
   if (whole) {
     hipLaunchKernelGGL((sdb::block_attn_f32_kernel<D, 2>), dim3(grid), dim3(64 * sdb::kF32Waves / 2), 0, st, a);
     return;
@@ -470,7 +462,7 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
     return fail(SD_ERR_INVALID_ARG, "q, caches and out must be 16-byte aligned");
   if (((uintptr_t)workspace & 255u) != 0) return fail(SD_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
   if (workspace_bytes < p.min_total)
-    return fail(SD_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, p.total);
+    return fail(SD_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, p.min_total);
   a->q = q;
   a->k = k_cache;
   a->v = v_cache;
@@ -482,7 +474,7 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
   a->part_ml = (float2 *)(ws + p.off_ml);
   a->part_o = (float *)(ws + p.off_o);
   a->bal = 0;  // bf16: the calls turn it on where the plan says so
-  a->bal_grid = p.bal_grid;
+  a->bal_grid = kBalGrid;
   a->group_mt = a->groups = 0;
   a->plan = nullptr;
   a->part_rows = p.part_rows;
@@ -517,7 +509,7 @@ int attn_args(const sd_attn_shape *sh, const AttnPlan &p, const void *q, const v
   a->block_table = nullptr;
   a->page_log2 = a->max_pages = a->num_pages = 0;
   a->k_new = a->v_new = nullptr;
-  a->bal_min_tiles = sh->dtype == SD_BF16 ? kBalMinTiles : kBalMinTilesF32;
+  a->bal_min_tiles = sh->dtype == SD_BF16 ? kBalMinTiles : sdb::kF32MinTiles;
   a->bal_kt = sh->dtype == SD_BF16 ? kBf16KT : sdb::kF32KT;
   return ok();
 }
