@@ -490,9 +490,11 @@ def _accept_ok(target_logits, draft_logits, draft_tokens, uniforms, block_lens, 
                                      block_lens.shape[0], torch.int32)
     n = total_q - S  # drafted tokens; more entries may be passed, and no draft row exists where there are none
     return (dev >= 0 and target_logits.is_contiguous() and _ok(block_lens, dev, i32, (S,))
-            and _ok(q_offsets, dev, i32, (S + 1,)) and type(draft_tokens) is torch.Tensor and draft_tokens.dim() == 1
-            and draft_tokens.shape[0] >= n and _ok(draft_tokens, dev, i32, draft_tokens.shape)
-            and (not sample or (((draft_logits is None and n <= 0) or _ok(draft_logits, dev, dt, (n, V)))
+            and _ok(q_offsets, dev, i32, (S + 1,))
+            and (_ok(draft_tokens, dev, i32, (n,))
+                 or (type(draft_tokens) is torch.Tensor and draft_tokens.dim() == 1 and draft_tokens.shape[0] > n
+                     and _ok(draft_tokens, dev, i32, draft_tokens.shape)))
+            and (not sample or ((_ok(draft_logits, dev, dt, (n, V)) or (draft_logits is None and n <= 0))
                                 and _ok(uniforms, dev, torch.float32, (total_q,))))
             and (accept_len is None or _ok(accept_len, dev, i32, (S,)))
             and (next_token is None or _ok(next_token, dev, i32, (S,))))
