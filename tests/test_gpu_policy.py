@@ -48,9 +48,14 @@ def test_vocab_not_a_chunk_multiple_and_wide_radius():
 
 @pytest.mark.parametrize("P", [1, 5, 11])
 def test_qwen3_vocab_hidden_2048(P):
-    """The paper's predictor: V = 151936 (Qwen3), two hidden layers of 2048, k = 2 around B = 16;
-    11 prompts exercise two groups of the dense passes."""
-    _check(W.make_policy(63 + P, P=P, V=151936, H=2048, radius=2, dtype="bf16"))
+    """The paper's predictor: V = 151936 (Qwen3), two hidden layers of 2048, k = 2 around B = 16; one
+    pass of the matrix layers, and with a workspace of the dense kernels' size those (11 prompts: two
+    groups of their passes)."""
+    pp = W.make_policy(63 + P, P=P, V=151936, H=2048, radius=2, dtype="bf16")
+    sc, _ = _check(pp)
+    dense, _ = _call(pp, _dense_bytes(P, 2048))
+    # both within the fp64 oracle's band of 1e-4 + 1e-4 |o|, so within twice that of each other
+    assert (np.abs(sc - dense) <= 2e-4 + 2e-4 * np.abs(dense)).all()
 
 
 def _dense_bytes(P, H):
@@ -74,7 +79,8 @@ def _call(pp, ws=None):
                                          (2, 1000, 64, "bf16")])
 def test_matrix_layers_edges(P, V, H, dtype):
     """Vocabularies below, at and past a 64-element tile, partial rows of the 64- and 512-row groups
-    and of the 16-row tiles, one more prompt than a pass holds; and the dense kernels, which a
+    and of the 16-row tiles, one more prompt than a pass holds (up to four prompts take the dense
+    kernels here: test_layers_rule_edges has these edges with more); and the dense kernels, which a
     workspace of their size alone still gets, on the same inputs."""
     pp = W.make_policy(80 + P, P=P, V=V, H=H, radius=2, dtype=dtype)
     sc, _ = _check(pp)
