@@ -322,3 +322,14 @@ def test_f32_whole_pairs_edges(S, Hq, Hkv, D, ctx, B, mask):
     """The fp32 kernel without splits (at most 192 keys, or 1024 with more than 256 groups) at the edges of
     its slots, tiles, groups and rule; rows past a sequence's keys are NaN in the cache."""
     G.check_attn(_f32(31 + S, S, Hq, Hkv, D, ctx, B, mask))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,Hq,Hkv,ctx,B,mask", [
+    (3, 4, 1, [191, 128, 256], [1, 64, 4], BIDIR),              # 64-key tiles: short by none, one tile past
+    (2, 4, 4, [192, 193], [1, 1], CAUSAL),                      # just past the whole pairs; four tiles
+    (40, 8, 8, [(53 * i) % 1100 for i in range(40)], [i % 5 for i in range(40)], CAUSAL),  # more pairs than CUs, past 1024 keys
+])
+def test_f32_split_edges(S, Hq, Hkv, D, ctx, B, mask):
+    """The fp32 splits where the bound on the keys is past the whole pairs' rule, full and small workspace."""
+    test_f32_plan_edges(S, Hq, Hkv, D, ctx, B, mask)
