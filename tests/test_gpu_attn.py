@@ -295,7 +295,8 @@ def _f32(seed, S, Hq, Hkv, D, ctx, B, mask):
 ])
 def test_f32_plan_edges(S, Hq, Hkv, D, ctx, B, mask):
     """Every row of the fp32 plan's edges at the fp32 tolerance, and again with a workspace of the even
-    splits' size, which leaves fewer slots or none (whole pairs)."""
+    splits' size, which leaves fewer slots or none.  (Bounds of at most 192 keys, and the last case with
+    more pairs than CUs, take whole pairs either way; test_f32_split_edges has the splits' edges.)"""
     p = _f32(7 + S, S, Hq, Hkv, D, ctx, B, mask)
     G.check_attn(p)
     pairs, L, mpad = S * Hkv, p.max_ctx + p.max_block, -(-(Hq // Hkv) * p.max_block // 16) * 16
